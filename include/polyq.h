@@ -305,8 +305,8 @@ polyq_status polyq_gemm(const polyq_layout* layout, const void* packed, const in
  * m, items[i].y, ...) computes, with the same argument rules per item (x holds
  * bf16 bits here).  Items with the same x and perm share one permuted copy.
  *   workspace: at least polyq_gemm_batch_workspace_bytes(items, count, m)
- *   bytes of device scratch (the permuted copies, and for count == 1 the
- *   split partial sums as in polyq_gemm); contents on entry are ignored.  The
+ *   bytes of device scratch (the permuted copies, and the split partial sums
+ *   of every item as in polyq_gemm); contents on entry are ignored.  The
  *   query reads the layout, x and perm fields; 0 on an invalid request or
  *   when no scratch is needed.
  */

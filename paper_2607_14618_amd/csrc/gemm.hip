@@ -3,40 +3,46 @@
 //
 // Prefill is a dense contraction, so it runs on the bf16 matrix cores
 // (v_mfma_f32_16x16x32_bf16, fp32 accumulation).  A work-group of 8 waves owns
-// 256 tokens x 128 weight rows (two packed tiles) and walks K one 32-channel
-// chunk at a time through a two-stage LDS ring:
-//   * every thread prefetches, three chunks ahead of their multiply (two
-//     register slots), 32 bytes of activations and
-//     its share of the packed chunk (8 codes of one row: one row sub-tile of
-//     one lane slice) plus that row's zero point and scale;
-//   * the packed share is dequantized once per work-group into a bf16 tile in
-//     LDS that all waves multiply (weights are the MFMA A operand, activations
-//     the B operand);
-//   * wave (tq, rt) multiplies rows 64 rt.. by tokens 64 tq..: 16 MFMAs per
-//     chunk; one barrier per chunk.
-// The loop is specialized per bit-width: a block's chunks run through the
-// copy of the loop compiled for its bit-width, one 128-channel group per
-// iteration, so the unpack, the group start and the group fold are fixed at
-// compile time and a step's common path has no branch.  The blocks (whose
-// bit-widths ascend) are visited by straight-line code, one copy per
-// bit-width, so that no loop carries the accumulators through every copy.
-// Each block starts in LDS stage 0, so chunk i of a group always sits in
-// stage i & 1 (compile-time addresses).  In the steady part of a block a
-// thread fetches exactly the packed words it unpacks (4, 8, 12 or 16 bytes)
-// and each step's instructions are issued in a fixed interleaving: fragment
-// reads, then every MFMA followed by part of the next chunk's dequantization.
+// four packed tiles (256 weight rows) x 16 NT tokens and walks K one
+// 128-channel group at a time:
+//   * wave (t, h) multiplies rows 32 h .. 32 h + 31 of packed tile t by all of
+//     the work-group's tokens.  Its weights never pass through LDS: a packed
+//     lane slice holds exactly the A fragments of that lane, so the wave loads
+//     its half of each slice two groups ahead into registers, dequantizes the
+//     group into eight fragments and multiplies them by every token tile;
+//   * the activations of the group (16 NT tokens x 256 bytes) are the B operand
+//     that all waves read from a two-stage LDS ring, loaded one group ahead.
+// One barrier per group.  The two waves of a SIMD (h = 0 and h = 1) run half a
+// group apart: one dequantizes behind the barrier, the other before it, so that
+// the vector ALU work of one overlaps the matrix work of the other (without:
+// 747 us instead of 681, gate/up of 2000 tokens x 13824 rows x 5120 channels).
+//
+// What bounds it: the issue slots and dependent chains of the two waves a SIMD
+// holds (248 registers at NT = 8).  A 16x16x32 MFMA takes two of its sixteen
+// clocks' four issue slots, so a group's 64 products and about 270 vector
+// instructions per wave (dequantization 150, folds 64) need 3200 of the 4900
+// clocks that it takes; the matrix pipes are 40 % busy.  Loads are not it: with
+// every load hitting the cache the launch is 3 % faster.  Measured against the
+// kernel before (256 tokens x 128 rows, both operands staged in LDS, whatever
+// M is), packed size and mix as stated: 33 tokens through a 13B-class layer (4
+// launches, 4 bits) 306 -> 131 us, 512 tokens 538 -> 451 us (720 TFLOP/s), 2000
+// tokens of gate/up at 3 bits 749 -> 649 us (870 TFLOP/s).  Also tried: four
+// waves per work-group and two work-groups per CU (734 us instead of 681), one
+// loop for all bit-widths (735: the weights' loads then go one group ahead
+// only), a second copy of the products for full groups or for the rare zero
+// points (spills).
 //
 // Numerics.  The dequantized operand is (q - z), an integer of magnitude
 // <= 255 that bf16 holds exactly when z is an integer in [0, 255]; each
 // 128-channel group accumulates into its own fp32 tile, which is then scaled
 // by the row's fp16 scale s (fp32 FMA) into the output accumulator.  A code
 // field at bit f of a half-word, OR-ed with the fp16 exponent field 25 - f,
-// reads as the fp16 value 2^(10-f) + q (exact), and one packed fp16 add of
-// -(2^(10-f) + z) leaves q - z exactly for such z; the bf16 value is the upper
-// half of its fp32 conversion.  A 16-bit channel, or a group whose zero point
-// is not such an integer, enters as the pair hi + lo of bf16 values (two
-// MFMAs): for fp16 weights the pair is exact; for any other z, q is recovered
-// exactly in fp32 and q - z rounds once before the split.
+// reads as the fp16 value 2^(10-f) + q (exact); converted to fp32 with
+// -(2^(10-f) + z) added in the same instruction it is q - z exactly for such z,
+// and so is its upper half, the bf16 value.  A 16-bit channel, or a group whose zero point
+// is not such an integer, enters as the pair hi + lo of bf16 values (a second
+// pass over the group): for fp16 weights the pair is exact; for any other z, q
+// is recovered exactly in fp32 and q - z rounds once before the split.
 #include <hip/hip_runtime.h>
 
 #include <string.h>
@@ -57,42 +63,42 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u3v __attribute__((ext_vector_type(3)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 
-constexpr int kTokWG = 256;                 // tokens per work-group
-constexpr int kRowsWG = 2 * kTileRows;      // weight rows per work-group (two packed tiles)
-constexpr int kThreads = 512;               // 8 waves
-constexpr int kLdsRow = 48;                 // bf16 per LDS row: 32 channels + 16 pad (96-byte rows: fewest bank conflicts measured among 16-byte-aligned strides)
-constexpr int kStageA = kTokWG * kLdsRow;   // bf16 of one activation stage
-constexpr int kStageB = kRowsWG * kLdsRow;  // bf16 of one weight tile (hi or lo) of a stage
+constexpr int kThreads = 512;      // 8 waves
+constexpr int kTilesWG = 4;        // packed tiles per work-group (two waves each)
+constexpr int kTok = 16;           // tokens of one MFMA
+constexpr int kMaxNT = 8;          // token tiles per work-group (kernel instances 1 .. kMaxNT)
+constexpr int kMaxSplits = 32;
 
-// One linear of a launch.
+// One linear of a launch: 64 dwords, so that one vector load (a dword per lane)
+// fetches it and v_readlane reads its fields at run-time indexes: scalar loads
+// of it missed the scalar cache line by line, one round trip after the other
+// (77 tokens x 1357 rows x 2976 channels: most of the launch).  Byte offsets
+// fit 31 bits (the host refuses larger packed buffers).
 struct GemmItem {
   const uint8_t* packed;
   const uint16_t* x;  // bf16 [m][k], clustered order
-  float* y;           // fp32 [m][n]
-  int32_t n, k, nblocks, n_tiles, n_chunks;
-  int32_t y_vec;  // rows of y can take 16-byte stores (n % 4 == 0, y 16-byte aligned)
+  float* y;           // fp32 [m][n]; splits > 1: the partial sums [splits][m][n]
+  int32_t n, k, nblocks, n_tiles;
+  int32_t groups;     // 128-channel groups (of every bit-width, 16 included)
+  int32_t y_vec;      // rows of y can take 16-byte stores (n % 4 == 0, y 16-byte aligned)
+  int32_t row_blocks; // ceil(n_tiles / kTilesWG)
   int32_t bits[POLYQ_MAX_BLOCKS];
-  int32_t cb[POLYQ_MAX_BLOCKS];  // first chunk of each block
-  int32_t ce[POLYQ_MAX_BLOCKS];  // end chunk of each block
-  int32_t pad;
-  int64_t off[POLYQ_MAX_BLOCKS];
-  int64_t tb[POLYQ_MAX_BLOCKS];  // bytes of one packed tile of the block
-  int64_t rb[POLYQ_MAX_BLOCKS];  // bytes of one group record (meta + 4 chunks)
+  int32_t len[POLYQ_MAX_BLOCKS];   // channels
+  int32_t k0[POLYQ_MAX_BLOCKS];    // first channel
+  int32_t off[POLYQ_MAX_BLOCKS];   // byte offset of the block region
+  int32_t tb[POLYQ_MAX_BLOCKS];    // bytes of one packed tile of the block
+  int32_t pad[26];
 };
+static_assert(sizeof(GemmItem) == 256, "argument record");
 
 // A launch: the linears' work-groups one after another (item i owns
-// work-groups wg_begin[i] .. wg_begin[i + 1] - 1), all with the same m.
-// K is split (count == 1 only) into `splits` chunk ranges starting at group
-// boundaries (split_chunk, unused when splits == 1); split s writes its sums
-// to partial[s][m][n] and a second kernel adds the splits in order.
-constexpr int kMaxSplits = 8;
-
+// work-groups wg_begin[i] .. wg_begin[i + 1] - 1), all with the same m.  K is
+// split into `splits` ranges of whole groups; with more than one, split s
+// writes its sums to y[s][m][n] and a second kernel adds the splits in order.
 struct GemmBatchArgs {
   GemmItem item[POLYQ_MAX_BATCH];
   int32_t count, m, m_tiles, splits;
   int32_t wg_begin[POLYQ_MAX_BATCH + 1];
-  int32_t split_chunk[kMaxSplits + 1];
-  float* partial;
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
@@ -100,19 +106,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
                                            static_cast<int>(bytes), 0x00020000);
 }
 
-// Prefetched data of one chunk for one thread.
-struct Pre {
-  u4v av[2];     // two 16-byte activation pieces
-  u4v w;         // 16 bytes at this thread's row sub-tile of its lane slice (b bytes used, 12 for 3 bits)
-  uint32_t z, s; // fp16 zero point and scale of the thread's row (loaded at a group's first chunk)
-};
-
 __host__ __device__ constexpr uint32_t exp_field(int e) { return (static_cast<uint32_t>(e) << 10) * 0x00010001u; }
 
 // The fields at bits f and 16 + f of w (mask m2 covers both, already shifted
 // to f) as the fp16 pair (2^(10-f) + q_even, 2^(10-f) + q_odd).
 __device__ __forceinline__ uint32_t field_pair(uint32_t w, uint32_t m2, int f) {
-  return (w & m2) | exp_field(25 - f);
+  // one v_and_or_b32 (a VOP3 takes no literal: the mask in an SGPR, the exponent in a VGPR)
+  uint32_t r;
+  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(w), "s"(m2), "v"(exp_field(25 - f)));
+  return r;
 }
 
 // The 4 code pairs (channels 2j, 2j+1) of row sub-tile r of a lane slice, in
@@ -196,453 +198,556 @@ __device__ __forceinline__ uint32_t hi_half_pair(float lo, float hi) {
                                0x07060302u);
 }
 
-// fp32 -> bf16 bits, round to nearest even (finite inputs).
-__device__ __forceinline__ uint32_t bf16_rne(float f) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, f);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 
-// Eight values of one row as the bf16 pair hi (nearest) + lo (nearest to the
-// remainder).
-__device__ __forceinline__ void store_pair(const float* v, uint16_t* hi_dst, uint16_t* lo_dst) {
-  uint32_t hb[8], lb[8];
+// Eight values as bf16: the nearest (hi), or the nearest to the remainder (lo).
+__device__ __forceinline__ u4v bf16_part(const float* v, bool lo) {
+  u4v r;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    hb[i] = bf16_rne(v[i]);
-    lb[i] = bf16_rne(v[i] - __builtin_bit_cast(float, hb[i] << 16));
+  for (int i = 0; i < 4; ++i) {
+    const float a = v[2 * i], b = v[2 * i + 1];
+    uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, bf16x2));
+    if (lo)
+      h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a - __builtin_bit_cast(float, h << 16),
+                                                                  b - __builtin_bit_cast(float, h & 0xFFFF0000u)}, bf16x2));
+    r[i] = h;
   }
-  *reinterpret_cast<uint4*>(hi_dst) =
-      uint4{hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16)};
-  *reinterpret_cast<uint4*>(lo_dst) =
-      uint4{lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16), lb[4] | (lb[5] << 16), lb[6] | (lb[7] << 16)};
+  return r;
 }
 
-// Byte offset of row sub-tile r inside a lane slice of a b-bit chunk (the
-// word(s) holding its codes; 3-bit slices are read whole).
-__device__ __forceinline__ int sub_offset(int b, int r) {
-  return b == 2 ? (r >> 1) * 4 : b == 4 ? r * 4 : b == 8 ? r * 8 : b == 16 ? r * 16 : 0;
+// One group of one wave in flight: its half of four lane slices, the zero points of the
+// lane's rows 16 (2h) + l%16 and 16 (2h+1) + l%16, and the scales of rows
+// 16 r + 4 (l/16) + e.
+struct Raw {
+  uint32_t w[16];
+  uint32_t z;
+  u4v s;
+};
+
+template <int B>
+__device__ __forceinline__ int slice_voff(int lane, int h) {
+  return lane * 4 * B + (B == 2 ? 4 * h : B == 4 ? 8 * h : B == 8 ? 16 * h : B == 16 ? 32 * h : 0);
 }
+
+// Loads of the group at byte `rec` of the tile: `nch` chunks; absent ones
+// re-read the last (their activations are zero).
+template <int B>
+__device__ __forceinline__ void issue_raw(Raw& r, __amdgpu_buffer_rsrc_t rs, int lane, int h, int rec, int nch) {
+  const int voff = slice_voff<B>(lane, h);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int so = rec + (B <= 8 ? kMetaBytes : 0) + min(c, nch - 1) * 256 * B;
+    if constexpr (B == 3) {
+      const u3v v = __builtin_bit_cast(u3v, __builtin_amdgcn_raw_buffer_load_b96(rs, voff, so, 0));
+      r.w[4 * c] = v.x; r.w[4 * c + 1] = v.y; r.w[4 * c + 2] = v.z;
+    } else if constexpr (B == 4) {
+      const u2v v = __builtin_bit_cast(u2v, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, so, 0));
+      r.w[2 * c] = v.x; r.w[2 * c + 1] = v.y;
+    } else if constexpr (B == 8) {
+      const u4v v = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, so, 0));
+      r.w[4 * c] = v.x; r.w[4 * c + 1] = v.y; r.w[4 * c + 2] = v.z; r.w[4 * c + 3] = v.w;
+    } else {
+      r.w[c] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, so, 0);
+    }
+  }
+  if constexpr (B <= 8) {
+    r.z = __builtin_amdgcn_raw_buffer_load_b32(rs, (lane & 15) * 8 + 4 * h, rec, 0);
+    r.s = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(rs, 128 + (lane >> 4) * 32 + 16 * h, rec, 0));
+  }
+}
+
+// The words of row sub-tile r of a chunk, as unpack_sub_tile takes them, out
+// of the wave's half slice `w` (r = 2h or 2h + 1).
+template <int B>
+__device__ __forceinline__ u4v sub_words(const uint32_t* w, int rr) {
+  if constexpr (B == 2) return u4v{w[0], 0u, 0u, 0u};
+  else if constexpr (B == 4) return u4v{w[rr], 0u, 0u, 0u};
+  else if constexpr (B == 8) return u4v{w[2 * rr], w[2 * rr + 1], 0u, 0u};
+  else return u4v{w[0], w[1], w[2], 0u};
+}
+template <int B>
+constexpr int chunk_words() { return B == 2 ? 1 : B == 4 ? 2 : 4; }
+
+__device__ __forceinline__ float f16_of(uint32_t bits) {
+  return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(bits)));
+}
+
+// Zero points that the packed fp16 subtraction takes exactly.
+__device__ __forceinline__ bool z_exact(uint32_t zz) {
+  const float z0 = f16_of(zz), z1 = f16_of(zz >> 16);
+  return z0 == truncf(z0) && z0 >= 0.f && z0 <= 255.f && z1 == truncf(z1) && z1 >= 0.f && z1 <= 255.f;
+}
+
+// The two halves of an fp16 pair plus c, in fp32 (v_fma_mix_f32 by 1.0: the
+// conversion and the addition in one instruction each).
+__device__ __forceinline__ float lo_plus(uint32_t pair, float c) {
+  float d;
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(c));
+  return d;
+}
+__device__ __forceinline__ float hi_plus(uint32_t pair, float c) {
+  float d;
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(c));
+  return d;
+}
+
+// The group's weights as bf16 A fragments (q - z), a[rr][chunk], for integer
+// zero points in [0, 255].  H is the wave's half (3 bits: the positions of a
+// sub-tile's codes depend on it; other widths take H = 0 for both).
+template <int B, int H>
+__device__ __forceinline__ void dequant(const Raw& raw, u4v (&a)[2][4]) {
+  float nc[2][4];  // -(off + z)
+#pragma unroll
+  for (int rr = 0; rr < 2; ++rr) {
+    const float z = f16_of(rr ? raw.z >> 16 : raw.z);
+    float off[4];
+    pair_offsets<B>(2 * H + rr, off);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nc[rr][j] = -off[j] - z;
+  }
+  // A chunk in three stages of independent instructions (a dependent VALU
+  // instruction waits about twice as long as an independent one; the fences
+  // keep the compiler from chaining them pair by pair).
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    uint32_t hp[2][4];
+    float lo[2][4], hi[2][4];
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) unpack_sub_tile<B>(sub_words<B>(&raw.w[c * chunk_words<B>()], rr), 2 * H + rr, hp[rr]);
+    __builtin_amdgcn_sched_barrier(0);
+    // (off + q) - (off + z) = q - z exactly in fp32, and in its upper half
+    // (bf16: |q - z| <= 255)
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lo[rr][j] = lo_plus(hp[rr][j], nc[rr][j]);
+        hi[rr][j] = hi_plus(hp[rr][j], nc[rr][j]);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr)
+      a[rr][c] = u4v{hi_half_pair(lo[rr][0], hi[rr][0]), hi_half_pair(lo[rr][1], hi[rr][1]),
+                     hi_half_pair(lo[rr][2], hi[rr][2]), hi_half_pair(lo[rr][3], hi[rr][3])};
+  }
+}
+
+// One chunk with any other zero points: (off + q) - off = q exactly, then
+// q - z rounds once; its hi or lo bf16 part.
+template <int B, int H>
+__device__ __forceinline__ void dequant_any(const uint32_t* w, uint32_t zz, bool lo, u4v (&out)[2]) {
+#pragma unroll
+  for (int rr = 0; rr < 2; ++rr) {
+    const float z = f16_of(rr ? zz >> 16 : zz);
+    float off[4], v[8];
+    uint32_t hp[4];
+    pair_offsets<B>(2 * H + rr, off);
+    unpack_sub_tile<B>(sub_words<B>(w, rr), 2 * H + rr, hp);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const h2 d = __builtin_bit_cast(h2, hp[j]);
+      v[2 * j] = (static_cast<float>(d.x) - off[j]) - z;
+      v[2 * j + 1] = (static_cast<float>(d.y) - off[j]) - z;
+    }
+    out[rr] = bf16_part(v, lo);
+  }
+}
+
+// The same for chunk c of a group re-read from memory.
+template <int B>
+__device__ __forceinline__ void reload_any(__amdgpu_buffer_rsrc_t rs, int lane, int h, int rec, int c, bool lo,
+                                           u4v (&out)[2]) {
+  const int voff = slice_voff<B>(lane, h), so = rec + kMetaBytes + c * 256 * B;
+  const uint32_t zz = __builtin_amdgcn_raw_buffer_load_b32(rs, (lane & 15) * 8 + 4 * h, rec, 0);
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < (B == 3 ? 3 : chunk_words<B>()); ++i)
+    w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff + 4 * i, so, 0);
+  if (B == 3 && h != 0)
+    dequant_any<B, 1>(w, zz, lo, out);
+  else
+    dequant_any<B, 0>(w, zz, lo, out);
+}
+
+// Dword `dw` of a 64-dword argument record held one dword per lane, as a
+// scalar (v_readlane; dw must be wave-uniform).
+template <class T>
+__device__ __forceinline__ T kfield(uint32_t kv, int dw) {
+  if constexpr (sizeof(T) == 8) {
+    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(kv, dw));
+    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(kv, dw + 1));
+    return __builtin_bit_cast(T, lo | (hi << 32));
+  } else {
+    return __builtin_bit_cast(T, static_cast<uint32_t>(__builtin_amdgcn_readlane(kv, dw)));
+  }
+}
+#define ITEM(T, field) kfield<T>(kv, offsetof(GemmItem, field) / 4)
+#define ITEM_AT(field, i) kfield<int32_t>(kv, offsetof(GemmItem, field) / 4 + (i))
 
 template <int V>
 using Int = std::integral_constant<int, V>;
 
+template <int NT>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmBatchArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t lds_a[2 * kStageA];      // [stage][token][channel]
-  __shared__ __attribute__((aligned(16))) uint16_t lds_b[2 * 2 * kStageB];  // [stage][hi, lo][row][channel]
-  __shared__ __attribute__((aligned(16))) float lds_r[2 * kRowsWG];         // [stage][row] group scale
-  __shared__ int lds_tag[2];  // chunk index + 1 when the stage holds a nonzero lo tile
+  constexpr int kStage = NT * kTok * 256;                // bytes of one LDS stage
+  constexpr int kPieces = (NT * 256 + kThreads - 1) / kThreads;  // 16-byte pieces per thread
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * kStage];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tq = wv & 3, rt = wv >> 2;  // MFMA role: token quarter, packed tile
-  // Token tile fastest: neighbouring work-groups (on different XCDs) share the
-  // weight rows, and each XCD's work-groups keep to a subset of token tiles.
+  const int h = wv >> 2;
+
+  // Work-group order: each XCD (work-groups go to the eight XCDs in turn) takes
+  // one contiguous stretch of the launch, token tile fastest, so that the
+  // token tiles that share weight rows also share an L2.
+  const int total = a.wg_begin[a.count];
+  const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
+  const int wg = xcd * per + min(xcd, rem) + static_cast<int>(blockIdx.x >> 3);
   int idx = 0;
 #pragma unroll
-  for (int i = 1; i < POLYQ_MAX_BATCH; ++i) idx += (i < a.count && static_cast<int>(blockIdx.x) >= a.wg_begin[i]) ? 1 : 0;
-  const GemmItem& it = a.item[idx];
-  const int local = static_cast<int>(blockIdx.x) - a.wg_begin[idx];
+  for (int i = 1; i < POLYQ_MAX_BATCH; ++i) idx += (i < a.count && wg >= a.wg_begin[i]) ? 1 : 0;
+  static_assert(offsetof(GemmBatchArgs, item) == 0, "argument layout");
+  const uint32_t* kargs = (const uint32_t*)(__builtin_amdgcn_kernarg_segment_ptr());
+  const uint32_t kv = kargs[idx * 64 + lane];
+  const uint8_t* packed = ITEM(const uint8_t*, packed);
+  const int nblocks = ITEM(int32_t, nblocks);
+  const int local = wg - a.wg_begin[idx];
   const int mt = local % a.m_tiles, rest = local / a.m_tiles;
-  const int ks = rest % a.splits, rp = rest / a.splits;
-  const int m0 = mt * kTokWG;
-  // this work-group's chunks [c0, C), c0 at a group boundary
-  const int c0 = a.splits > 1 ? a.split_chunk[ks] : 0;
-  const int C = a.splits > 1 ? a.split_chunk[ks + 1] : it.n_chunks;
-  int b0 = 0;
-#pragma unroll
-  for (int j = 0; j < POLYQ_MAX_BLOCKS - 1; ++j) b0 += (j + 1 < it.nblocks && c0 >= it.ce[j]) ? 1 : 0;
+  const int rb = rest % ITEM(int32_t, row_blocks), ks = rest / ITEM(int32_t, row_blocks);
+  const int m0 = mt * (NT * kTok);
+  const int groups = ITEM(int32_t, groups);
+  const int g0 = groups * ks / a.splits, g1 = groups * (ks + 1) / a.splits;
+  const int tile = rb * kTilesWG + (wv & 3);
+  const bool tile_ok = tile < ITEM(int32_t, n_tiles);
+  const int kdim = ITEM(int32_t, k);
 
-  // Dequantization role: packed tile dp, row sub-tile dr (wave-uniform), lane
-  // slice `lane`: row drow of the tile, channels 8 (lane / 16) .. + 7.
-  const int dp = wv >> 2, dr = wv & 3;
-  const int dt = rp * 2 + dp;
-  const bool dtile_ok = dt < it.n_tiles;
-  const int drow = 16 * dr + (lane & 15);
-  const int bst = (dp * 64 + drow) * kLdsRow + 8 * (lane >> 4);  // LDS slot of its 8 weights
-  const int sst = dp * 64 + drow;                                  // LDS slot of its row's scale
-
-  // Activations: buffer over rows m0 .. m0 + 255 of x' (reads past row m - 1
-  // return zero); piece j of this thread is token piece/4, 16-byte segment piece%4.
+  // ---- Activations: buffer over this token tile's rows (reads past row m - 1
+  // return zero).  Stage layout: blocks of 8 tokens x 128 bytes (two chunks),
+  // the 16-byte pieces of a token XOR-swizzled by token % 8, so that neither
+  // the stores (8 lanes fill one row) nor the fragment reads (8 lanes read one
+  // piece of 8 rows) conflict.
+  const int rows = min(a.m - m0, NT * kTok);
   const __amdgpu_buffer_rsrc_t xrs =
-      make_rsrc(it.x + static_cast<int64_t>(m0) * it.k, static_cast<uint32_t>(min(a.m - m0, kTokWG)) * it.k * 2u);
-  uint32_t avoff[2];
-  int ast[2];
+      make_rsrc(ITEM(const uint16_t*, x) + static_cast<int64_t>(m0) * kdim, static_cast<uint32_t>(rows) * kdim * 2u);
+  u4v xr[kPieces];
+  // this thread's pieces: piece (tid & 7) of chunk pair (tid >> 6) & 1 of token
+  // tid / 128 * 8 + tid / 8 % 8, and of the tokens 32, 64, .. further on
+  const int xseg = ((tid >> 6) & 1) * 8 + (tid & 7);
+  const int xvoff = (((tid >> 7) * 8 + ((tid >> 3) & 7)) * kdim + xseg * 8) * 2;
+  // (`chan`: the group's first channel, nch: its chunks)
+  auto load_x = [&](int chan, int nch) __attribute__((always_inline)) {
+    // a chunk past the group's end reads zeros (an offset past the buffer)
+    const int voff = (xseg >> 2) < nch ? xvoff : 0x40000000;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int piece = tid + j * kThreads;
-    avoff[j] = (static_cast<uint32_t>(piece >> 2) * it.k + (piece & 3) * 8) * 2u;
-    ast[j] = (piece >> 2) * kLdsRow + (piece & 3) * 8;
-  }
-  // MFMA fragment reads: tokens 64 tq + 16 j + lane%16 (B), rows 64 rt + 16 i + lane%16 (A)
-  const int ard = (tq * 64 + (lane & 15)) * kLdsRow + 8 * (lane >> 4);
-  const int brd = (rt * 64 + (lane & 15)) * kLdsRow + 8 * (lane >> 4);
+    for (int i = 0; i < kPieces; ++i)
+      xr[i] = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(xrs, voff + i * (64 * kdim), chan * 2, 0));
+  };
+  auto store_x = [&](int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      const int p = tid + i * kThreads;
+      const int t8 = (p >> 3) & 7;
+      const int at = (((p >> 6) & 1) * (NT * 2) + (p >> 7)) * 1024 + t8 * 128 + (((p & 7) ^ t8) * 16);
+      if (NT % 2 == 0 || p < NT * 256) *reinterpret_cast<u4v*>(lds + stage * kStage + at) = xr[i];
+    }
+  };
+  // this lane's piece of token l%16 of a token tile, chunk 0 (and, ^ 64, chunk 1)
+  const int frag0 = ((lane >> 3) & 1) * 1024 + (lane & 7) * 128 + (((lane >> 4) ^ (lane & 7)) * 16);
 
-  // Load cursor: the next chunk to fetch, its block and a buffer over this
-  // thread's packed tile of that block (no records for a tile past the end,
-  // so its reads return zero).  Block-generic: it runs ahead of the
-  // bit-width-specialized loop across block boundaries.
-  int lc = c0, lb = 0, lcl = 0, lbits = 0, lce = 0, lrb = 0;
-  uint32_t lvoff = 0;
+  // ---- The walk over the groups [g0, g1): a position is a block, a group of
+  // it and how many groups of the split follow; it stays on the split's last
+  // group, so that the loads ahead of the multiplication are unconditional
+  // (every wait then knows how many younger loads are in flight).
+  struct Walk {
+    int block, bits, chan, end, left;
+  };
+  auto enter = [&](Walk& w, int block, int g) __attribute__((always_inline)) {
+    w.block = block;
+    w.bits = ITEM_AT(bits, block);
+    w.chan = ITEM_AT(k0, block) + g * kGroup;
+    w.end = ITEM_AT(k0, block) + ITEM_AT(len, block);
+  };
+  auto advance = [&](Walk& w) __attribute__((always_inline)) {
+    if (w.left == 0) return;
+    --w.left;
+    w.chan += kGroup;
+    if (w.chan >= w.end) enter(w, w.block + 1, 0);
+  };
+  auto nch_of = [&](const Walk& w) __attribute__((always_inline)) { return min(kGroup, w.end - w.chan) / kChunk; };
+  const int ng = g1 - g0;
+  Walk wx, wr;  // the next group of the activations' loads and of the weights'
+  int rec;      // byte of wr's group in its packed tile
   __amdgpu_buffer_rsrc_t wrs;
-  auto set_block = [&](int b) __attribute__((always_inline)) {
-    lb = b;
-    lbits = it.bits[b];
-    lce = it.ce[b];
-    lrb = static_cast<int>(it.rb[b]);
-    const int64_t tb = it.tb[b];
-    wrs = make_rsrc(it.packed + it.off[b] + static_cast<int64_t>(dtile_ok ? dt : 0) * tb,
-                    dtile_ok ? static_cast<uint32_t>(tb) : 0u);
-    lvoff = static_cast<uint32_t>(lane * 4 * lbits + sub_offset(lbits, dr));
-    lcl = 0;
+  auto locate = [&]() __attribute__((always_inline)) {
+    rec = ((wr.chan - ITEM_AT(k0, wr.block)) / kGroup) * ((wr.bits <= 8 ? kMetaBytes : 0) + 1024 * wr.bits);
+    wrs = make_rsrc(packed + ITEM_AT(off, wr.block) + static_cast<int64_t>(tile_ok ? tile : 0) * ITEM_AT(tb, wr.block),
+                    tile_ok ? static_cast<uint32_t>(ITEM_AT(tb, wr.block)) : 0u);
   };
-  const uint32_t zvoff = 2 * meta_z_half(drow), svoff = 2 * meta_s_half(drow);
-  auto load = [&](Pre& pr) __attribute__((always_inline)) {
+  auto advance_weights = [&]() __attribute__((always_inline)) {
+    const int block = wr.block, chan = wr.chan;
+    advance(wr);
+    if (wr.block != block) locate();
+    else if (wr.chan != chan) rec += (wr.bits <= 8 ? kMetaBytes : 0) + 1024 * wr.bits;
+  };
+
+  u4v af[2][4];
+  f4 sc[2];
+  f4 T[NT][2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      pr.av[j] = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(xrs, avoff[j], lc * 64, 0));
-    const int rec = (lcl >> 2) * lrb;
-    const int soff = rec + (lbits <= 8 ? kMetaBytes : 0) + (lcl & 3) * 256 * lbits;
-    pr.w = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(wrs, lvoff, soff, 0));
-    // the row's z and s of the chunk's group (used at a group's first chunk;
-    // loaded for every chunk, so that every slot has the same loads in flight
-    // and each wait can leave the younger slot's loads outstanding)
-    pr.z = __builtin_amdgcn_raw_buffer_load_b16(wrs, zvoff, rec, 0);
-    pr.s = __builtin_amdgcn_raw_buffer_load_b16(wrs, svoff, rec, 0);
-    ++lc;
-    ++lcl;
-    if (lc == lce && lc < C) set_block(lb + 1);
-  };
-  // The same for a chunk known to lie in the current block, of bit-width B:
-  // the packed words are fetched with a load of exactly their size (4, 8, 12
-  // or 16 bytes), which the memory pipeline serves faster than a 16-byte load
-  // at a 4-byte offset, and no block boundary is checked.  The row's z and s
-  // are fetched only for a group's first chunk (`zs`, known at compile time
-  // in the steady loop): their 2-byte loads, four lanes to an address, cost
-  // the memory pipeline about as much as the activations' 16-byte loads.
-  auto load_in_block = [&](auto b_tag, Pre& pr, bool zs) __attribute__((always_inline)) {
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) T[j][rr] = f4{0.f, 0.f, 0.f, 0.f};
+
+  // The hi or lo fragments of a group with a zero point that is not an integer
+  // in [0, 255], re-read from memory.
+  auto reload = [&](auto b_tag, __amdgpu_buffer_rsrc_t rs, int rec, int nch, bool lo) __attribute__((always_inline)) {
     constexpr int B = decltype(b_tag)::value;
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {  // rotates: after four rounds chunk c is in slot c
+      u4v o[2];
+      reload_any<B>(rs, lane, h, rec, min(c, nch - 1), lo, o);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      pr.av[j] = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(xrs, avoff[j], lc * 64, 0));
-    const int rec = (lcl >> 2) * lrb;
-    const int soff = rec + (B <= 8 ? kMetaBytes : 0) + (lcl & 3) * 256 * B;
-    if constexpr (B == 16) {
-      pr.w = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(wrs, lvoff, soff, 0));
-    } else if constexpr (B == 8) {
-      const u2v v = __builtin_bit_cast(u2v, __builtin_amdgcn_raw_buffer_load_b64(wrs, lvoff, soff, 0));
-      pr.w = u4v{v.x, v.y, 0u, 0u};
-    } else if constexpr (B == 3) {
-      const u3v v = __builtin_bit_cast(u3v, __builtin_amdgcn_raw_buffer_load_b96(wrs, lvoff, soff, 0));
-      pr.w = u4v{v.x, v.y, v.z, 0u};
-    } else {
-      pr.w = u4v{__builtin_amdgcn_raw_buffer_load_b32(wrs, lvoff, soff, 0), 0u, 0u, 0u};
-    }
-    if (zs) {
-      pr.z = __builtin_amdgcn_raw_buffer_load_b16(wrs, zvoff, rec, 0);
-      pr.s = __builtin_amdgcn_raw_buffer_load_b16(wrs, svoff, rec, 0);
-    }
-    ++lc;
-    ++lcl;
-  };
-
-  // Group state of the thread's row while its group is being stored: scale,
-  // zero point, whether every zero point of the wave is an integer in
-  // [0, 255] (wave-uniform), and the pair constants -(off[j] + z).
-  float gs = 0.f, gz = 0.f;
-  bool gexact = true;
-  h2 gc[4];
-  // bit st: this thread's lo slot of stage st may hold nonzero values (a
-  // 16-bit chunk or a pair-stored group used it); cleared before an exact
-  // store into the stage, since a stage's second MFMA pass reads every row.
-  uint32_t lo_dirty = 0;
-
-  // Dequantize one chunk (prefetched in pr) into stage st, with its rows'
-  // group scales.  first: the chunk starts a group (its z and s are in pr).
-  // The exact form (integer zero points) is always written, without
-  // branches; store_fix then rewrites the chunk as hi + lo pairs in a wave
-  // whose zero points are not all such integers.
-  auto store_main = [&](auto b_tag, const Pre& pr, int c, int st, bool first) __attribute__((always_inline)) {
-    constexpr int B = decltype(b_tag)::value;
-    uint16_t* sa = lds_a + st * kStageA;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) *reinterpret_cast<u4v*>(sa + ast[j]) = pr.av[j];
-    uint16_t* hi = lds_b + st * 2 * kStageB + bst;
-    uint16_t* lo = hi + kStageB;
-    if constexpr (B == 16) {
-      lds_r[st * kRowsWG + sst] = 1.f;  // the four threads of a row store the same value
-      const uint32_t ww[4] = {pr.w.x, pr.w.y, pr.w.z, pr.w.w};
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const h2 h = __builtin_bit_cast(h2, ww[i]);
-        v[2 * i] = static_cast<float>(h.x);
-        v[2 * i + 1] = static_cast<float>(h.y);
-      }
-      store_pair(v, hi, lo);
-      lo_dirty |= 1u << st;
-      return;
-    }
-    if (first) {
-      float off[4];
-      pair_offsets<B>(dr, off);
-      gz = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(pr.z)));
-      gs = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(pr.s)));
-      gexact = __all(gz == truncf(gz) && gz >= 0.f && gz <= 255.f);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const _Float16 cz = static_cast<_Float16>(-(off[j] + gz));  // exact when gexact
-        gc[j] = h2{cz, cz};
+      for (int rr = 0; rr < 2; ++rr) {
+        af[rr][0] = af[rr][1];
+        af[rr][1] = af[rr][2];
+        af[rr][2] = af[rr][3];
+        af[rr][3] = o[rr];
       }
     }
-    lds_r[st * kRowsWG + sst] = gs;
-    uint32_t hp[4];
-    unpack_sub_tile<B>(pr.w, dr, hp);
-    // (off + q) - (off + z) = q - z exactly in fp16 (|q - z| <= 255), and
-    // exactly again in fp32 and in its upper half (bf16)
-    uint32_t o[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const h2 d = __builtin_bit_cast(h2, hp[j]) + gc[j];
-      o[j] = hi_half_pair(static_cast<float>(d.x), static_cast<float>(d.y));
-    }
-    *reinterpret_cast<uint4*>(hi) = uint4{o[0], o[1], o[2], o[3]};
   };
-  auto store_fix = [&](auto b_tag, const Pre& pr, int c, int st) __attribute__((always_inline)) {
-    constexpr int B = decltype(b_tag)::value;
-    uint16_t* hi = lds_b + st * 2 * kStageB + bst;
-    uint16_t* lo = hi + kStageB;
-    if constexpr (B == 16) {
-      if (tid == 0) lds_tag[st] = c + 1;
-      return;
-    }
-    if (__builtin_expect(gexact, 1)) {
-      if (__builtin_expect(lo_dirty & (1u << st), 0)) {
-        *reinterpret_cast<uint4*>(lo) = uint4{0u, 0u, 0u, 0u};
-        lo_dirty &= ~(1u << st);
-      }
-      return;
-    }
-    // any other fp16 z: (off + q) - off = q exactly, then q - z rounds once
-    float off[4];
-    pair_offsets<B>(dr, off);
-    uint32_t hp[4];
-    unpack_sub_tile<B>(pr.w, dr, hp);
-    float v[8];
+  // All products of one group, in sets of up to four token tiles: the set's
+  // partial sums over the group's four chunks, then total += s * part, beside
+  // the next set's first products.  The fragments of a step (one chunk of a
+  // set) are read one step ahead; the fences keep the compiler from hoisting
+  // every read to the front (the registers would not hold them).  The wave's
+  // priority is raised meanwhile, so that the matrix pipe goes first and the
+  // SIMD's other wave unpacks in the slots it leaves (gate/up of 2000 tokens:
+  // 681 -> 676 us).
+  auto multiply = [&](int stage) __attribute__((always_inline)) {
+    constexpr int kSets = (NT + 3) / 4, kSteps = 4 * kSets;
+    const uint8_t* b0 = lds + stage * kStage + frag0;
+    const uint8_t* b1 = lds + stage * kStage + (frag0 ^ 64);
+    bf16x8 bf[2][4];
+    f4 P[4][2];
+    auto read = [&](int st) __attribute__((always_inline)) {
+      const int c = st & 3;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const h2 h = __builtin_bit_cast(h2, hp[j]);
-      v[2 * j] = (static_cast<float>(h.x) - off[j]) - gz;
-      v[2 * j + 1] = (static_cast<float>(h.y) - off[j]) - gz;
-    }
-    store_pair(v, hi, lo);
-    lo_dirty |= 1u << st;
-    lds_tag[st] = c + 1;  // any thread; every writer stores the same value
-  };
-
-  f4 T[4][4], P[4][4];  // output accumulators, the group's partial sums
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) T[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-
-  // MFMA pass over stage st: the hi tile (first: fresh partial sums) or the
-  // lo tile.
-  auto mfma_pass = [&](int st, bool first, int tile) __attribute__((always_inline)) {
-    const uint16_t* sa = lds_a + st * kStageA;
-    const uint16_t* sb = lds_b + st * 2 * kStageB + tile * kStageB;
-    bf16x8 af[4], bfr[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      af[i] = *reinterpret_cast<const bf16x8*>(sb + brd + i * 16 * kLdsRow);
-      bfr[i] = *reinterpret_cast<const bf16x8*>(sa + ard + i * 16 * kLdsRow);
-    }
-    if (first) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          P[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) P[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], P[i][j], 0, 0, 0);
-    }
-  };
-  // Group fold: total += s * part, s of rows 16 i + 4 (lane/16) + e
-  // (stage st holds the group's last chunk and its scales).
-  auto fold = [&](int st) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f4 sv = *reinterpret_cast<const f4*>(&lds_r[st * kRowsWG + rt * 64 + 16 * i + 4 * (lane >> 4)]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) T[i][j][e] = fmaf(sv[e], P[i][j][e], T[i][j][e]);
-    }
-  };
-
-  // A chunk sits in a register slot from its load (two chunks ahead) to its
-  // store (one chunk ahead), and in an LDS stage from its store to its
-  // multiply; both alternate chunk by chunk.  `sc` is the slot the next step
-  // stores from, `sn` the other (it holds the chunk after that); a step that
-  // ends a block leaves its slot, holding the next block's first chunk, for
-  // that block's entry.  The slots are named, not indexed, so that they stay
-  // in registers: after an odd number of steps their contents trade places.
-  Pre sc, sn;
-  if (tid < 2) lds_tag[tid] = 0;
-  *reinterpret_cast<uint4*>(lds_b + kStageB + bst) = uint4{0u, 0u, 0u, 0u};  // lo slots of both stages
-  *reinterpret_cast<uint4*>(lds_b + 3 * kStageB + bst) = uint4{0u, 0u, 0u, 0u};
-  set_block(b0);
-  lcl = c0 - it.cb[b0];
-  load(sn);
-  if (C - c0 > 1) load(sc);
-  __syncthreads();  // the tags and cleared lo slots before the first store
-  int c = c0;  // next chunk to multiply
-
-  // Chunks [c, cend) of one block of bit-width B, from a group boundary.  The
-  // loop is compiled per bit-width, one group of four chunks per iteration:
-  // the unpack, the group start and the group end are fixed at compile time
-  // and the common path of a step has no branch.
-  auto run_block = [&](auto b_tag, int cend) __attribute__((always_inline)) {
-    constexpr int B = decltype(b_tag)::value;
-    // entry: the block's first chunk, still in sn, into stage 0 (the last
-    // barrier left both stages free), so that stage indices are compile-time
-    // constants: chunk i of a group sits in stage i & 1
-    store_main(b_tag, sn, c, 0, true);
-    store_fix(b_tag, sn, c, 0);
-    if (c + 2 < C) load(sn);
-    __syncthreads();
-    // One step: multiply chunk c (stage st); if `more` (chunk c + 1 is in the
-    // block) store chunk c + 1 (`nf`: it starts a group) from `slot` into the
-    // other stage and fetch chunk c + 3 into it (`inner`: known to be in the
-    // split); fold a group that ends with chunk c.  `two`: the group's chunks
-    // carry lo tiles (every chunk of a group is stored the same way, since its
-    // zero points are the group's, so the tag is read at its first chunk).
-    bool two = B == 16;
-    auto step = [&](Pre& slot, int st, bool first, bool last, bool nf, bool more, bool inner,
-                    bool in_block = false, bool zs = true) __attribute__((always_inline)) {
-      if (B != 16 && first) two = __builtin_expect(lds_tag[st] == c + 1, 0);
-      mfma_pass(st, first, 0);
-      if (more) store_main(b_tag, slot, c + 1, st ^ 1, nf);
-      if (in_block) {
-        // issue order of a steady step: the eight fragment reads, then each
-        // MFMA followed by two VALU instructions of the next chunk's
-        // dequantization and, every few MFMAs, one of its LDS stores (the
-        // wave keeps its VALU and LDS work flowing while the matrix pipe is
-        // busy, instead of leaving it all after the MFMAs)
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-          if (m == 3 || m == 7 || m == 11 || m == 13) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        }
-      }
-      if (two) mfma_pass(st, false, 1);
-      if (last) fold(st);
-      if (more) {
-        store_fix(b_tag, slot, c + 1, st ^ 1);
-        if (in_block) load_in_block(b_tag, slot, zs);
-        else if (inner || c + 3 < C) load(slot);
-      }
-      ++c;
-      __syncthreads();
+      for (int u = 0; u < 4; ++u)
+        if (st / 4 * 4 + u < NT)
+          bf[st & 1][u] = *reinterpret_cast<const bf16x8*>((c & 1 ? b1 : b0) + (c >> 1) * (NT * 2048) + (st / 4 * 4 + u) * 2048);
     };
-    // Every group but the block's last: all four steps have their next chunk
-    // in the block and (three chunks ahead) in the split, so every step
-    // issues the same loads and each wait leaves the younger slot in flight.
-    // In all but the last two groups the chunk fetched (at most six ahead of
-    // the group's first) is in the block too.
-    const int nch = cend - c;
-    const int full = (nch - 1) / 4;
-    // (step i fetches chunk i + 3 of the group: only step 1's starts a group)
-    for (int g = full - 1; g > 0; --g) {
-      step(sc, 0, true, false, false, true, true, true, false);
-      step(sn, 1, false, false, false, true, true, true, true);
-      step(sc, 0, false, false, false, true, true, true, false);
-      step(sn, 1, false, true, true, true, true, true, false);
+    auto fold = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+      for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) T[j][rr][e] = fmaf(sc[rr][e], P[j & 3][rr][e], T[j][rr][e]);
+    };
+    read(0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+      const int c = st & 3, j0 = st / 4 * 4;
+      if (st + 1 < kSteps) read(st + 1);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (c == 0 && j0 > 0) fold(j0 - 4 + u);
+        if (j0 + u < NT)
+#pragma unroll
+          for (int rr = 0; rr < 2; ++rr)
+            P[u][rr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[rr][c]), bf[st & 1][u],
+                                                               c == 0 ? f4{0.f, 0.f, 0.f, 0.f} : P[u][rr], 0, 0, 0);
+      }
+      // issue order of a step: the next step's reads, then the products (a
+      // set's first step: each tile's fold before its products)
+      const int nr = st + 1 < kSteps ? std::min(4, NT - (st + 1) / 4 * 4) : 0;
+#pragma unroll
+      for (int u = 0; u < nr; ++u) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (c == 0 && j0 > 0) __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+        if (j0 + u < NT) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (full > 0) {
-      step(sc, 0, true, false, false, true, true);
-      step(sn, 1, false, false, false, true, true);
-      step(sc, 0, false, false, false, true, true);
-      step(sn, 1, false, true, true, true, true);
-    }
-    // The block's last group: 1 .. 4 chunks.
-    const int r = cend - c;
-    step(sc, 0, true, r == 1, false, r > 1, false);
-    if (r >= 2) step(sn, 1, false, r == 2, false, r > 2, false);
-    if (r >= 3) step(sc, 0, false, r == 3, false, r > 3, false);
-    if (r >= 4) step(sn, 1, false, true, false, false, false);
-    if (r & 1) {
-      const Pre t = sc;
-      sc = sn;
-      sn = t;
-    }
+#pragma unroll
+    for (int j = (kSets - 1) * 4; j < NT; ++j) fold(j);
+    __builtin_amdgcn_s_setprio(0);
   };
-  // Blocks have strictly ascending bit-widths, so the work-group's blocks are
-  // visited by one pass over the palette: straight-line code, no loop whose
-  // registers every bit-width's copy would have to share.
-  int bi = b0;
-  auto visit = [&](auto b_tag) __attribute__((always_inline)) {
-    constexpr int B = decltype(b_tag)::value;
-    if (c < C && it.bits[bi] == B) {
-      run_block(b_tag, min(it.ce[bi], C));
-      ++bi;
-    }
-  };
-  visit(Int<2>{});
-  visit(Int<3>{});
-  visit(Int<4>{});
-  visit(Int<8>{});
-  visit(Int<16>{});
 
-  // D layout: lane holds weight rows 16 i + 4 (lane/16) + e of token 16 j + lane%16.
-  const int row0 = (rp * 2 + rt) * kTileRows + 4 * (lane >> 4);
-  float* ybase = a.splits > 1 ? a.partial + static_cast<int64_t>(ks) * a.m * it.n : it.y;
-  const bool vec = a.splits > 1 ? (it.n & 3) == 0 : it.y_vec != 0;
+  // ---- Main loop.  Group i (of ng) sits in LDS stage i & 1; its activations
+  // are loaded during group i - 1, its weights two groups ahead.  The barrier
+  // of group i lets a wave read stage i & 1 and write the other one (every wave
+  // has finished group i - 1).
+  int i = 0;
+  // The groups of one block of bit-width B from group i on (in the split).
+  auto run_block = [&](auto b_tag) __attribute__((always_inline)) {
+    constexpr int B = decltype(b_tag)::value;
+    // the block's first two groups (the loads issued for them from the block
+    // before only brought their lines into L2)
+    const int block = wx.block;
+    Walk cur = wx;  // group i
+    if (i > 0) {
+      wr = wx;
+      locate();
+    }
+    Raw r0, r1;
+    issue_raw<B>(r0, wrs, lane, h, rec, nch_of(wr));
+    advance_weights();
+    issue_raw<B>(r1, wrs, lane, h, rec, nch_of(wr));
+    advance_weights();
+    advance(wx);
+    auto step = [&](Raw& raw) __attribute__((always_inline)) {
+      if (h == 0) __syncthreads();
+      const bool exact = __all(z_exact(raw.z));
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int tok = m0 + tq * 64 + 16 * j + (lane & 15);
+      for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[rr][e] = f16_of(raw.s[2 * rr + e / 2] >> (16 * (e & 1)));
+      if (B == 3 && h != 0) dequant<B, 1>(raw, af);
+      else dequant<B, 0>(raw, af);
+      load_x(wx.chan, nch_of(wx));
+      issue_raw<B>(raw, wrs, lane, h, rec, nch_of(wr));
+      advance_weights();
+      if (h != 0) __syncthreads();
+#pragma unroll 1
+      for (int pass = 0;; ++pass) {
+        if (__builtin_expect(!exact, 0)) {
+          const int cb = cur.block;
+          reload(b_tag,
+                 make_rsrc(packed + ITEM_AT(off, cb) + static_cast<int64_t>(tile_ok ? tile : 0) * ITEM_AT(tb, cb),
+                           tile_ok ? static_cast<uint32_t>(ITEM_AT(tb, cb)) : 0u),
+                 ((cur.chan - ITEM_AT(k0, cb)) / kGroup) * (kMetaBytes + 1024 * B), nch_of(cur), pass != 0);
+        }
+        multiply(i & 1);
+        if (exact || pass) break;
+      }
+      store_x((i + 1) & 1);
+      ++i;
+      cur = wx;
+      if (i == ng || wx.block != block) return false;
+      advance(wx);
+      return true;
+    };
+    while (step(r0) && step(r1)) {
+    }
+  };
+  // The groups of the 16-bit block: fp16 weights, hi then lo parts.  (Both
+  // parts come from registers: re-reading the weights for each, with the
+  // conversion in integer instructions, cost about 10 us per work-group.)
+  auto run_block16 = [&]() __attribute__((always_inline)) {
+    sc[0] = sc[1] = f4{1.f, 1.f, 1.f, 1.f};
+    for (;;) {
+      wr = wx;
+      locate();
+      const int nch = nch_of(wx);
+      u4v w[2][4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr)
+          w[rr][c] = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(
+              wrs, slice_voff<16>(lane, h) + 16 * rr, rec + min(c, nch - 1) * 4096, 0));
+      advance(wx);
+      load_x(wx.chan, nch_of(wx));
+      __syncthreads();
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = f16_of(w[rr][c][e / 2] >> (16 * (e & 1)));
+            af[rr][c] = bf16_part(v, pass != 0);
+          }
+        multiply(i & 1);
+      }
+      store_x((i + 1) & 1);
+      if (++i == ng) break;
+    }
+  };
+  if (ng > 0) {
+    int g = g0, b = 0;
+    while (b + 1 < nblocks && g >= (ITEM_AT(len, b) + kGroup - 1) / kGroup) {
+      g -= (ITEM_AT(len, b) + kGroup - 1) / kGroup;
+      ++b;
+    }
+    enter(wx, b, g);
+    wx.left = ng - 1;
+    wr = wx;
+    locate();
+    load_x(wx.chan, nch_of(wx));
+    store_x(0);
+    // bit-widths ascend: one pass over the palette, straight-line code
+    if (wx.bits == 2) run_block(Int<2>{});
+    if (i < ng && wx.bits == 3) run_block(Int<3>{});
+    if (i < ng && wx.bits == 4) run_block(Int<4>{});
+    if (i < ng && wx.bits == 8) run_block(Int<8>{});
+    if (i < ng && wx.bits == 16) run_block16();
+  }
+
+  // D layout: lane holds weight rows 16 rr + 4 (lane/16) + e of token 16 j + lane%16.
+  if (!tile_ok) return;
+  const int row0 = tile * kTileRows + 32 * h + 4 * (lane >> 4);
+  const int n = ITEM(int32_t, n);
+  const bool y_vec = ITEM(int32_t, y_vec) != 0;
+  float* ybase = ITEM(float*, y) + static_cast<int64_t>(ks) * a.m * n;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int tok = m0 + kTok * j + (lane & 15);
     if (tok >= a.m) continue;
-    float* yr = ybase + static_cast<int64_t>(tok) * it.n;
+    float* yr = ybase + static_cast<int64_t>(tok) * n;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = row0 + 16 * i;
-      if (vec && row + 3 < it.n) {
-        *reinterpret_cast<f4*>(yr + row) = T[i][j];
+    for (int rr = 0; rr < 2; ++rr) {
+      const int row = row0 + 16 * rr;
+      if (y_vec && row + 3 < n) {
+        *reinterpret_cast<f4*>(yr + row) = T[j][rr];
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (row + e < it.n) yr[row + e] = T[i][j][e];
+          if (row + e < n) yr[row + e] = T[j][rr][e];
       }
     }
   }
 }
 
-// y = partial[0] + partial[1] + ... (in split order), `count` elements each,
-// four consecutive elements per thread (16-byte accesses when count is a
-// multiple of 4 and y is 16-byte aligned; the partials always are).
-__global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict__ partial,
-                                                         float* __restrict__ y, int splits,
-                                                         int64_t count) {
+// y = partial[0] + partial[1] + ... (in split order) of every linear of a
+// launch (grid.y), `count` elements each, four consecutive elements per thread
+// (16-byte accesses when count is a multiple of 4 and y is 16-byte aligned; the
+// partials always are).
+struct SumArgs {
+  const float* partial[POLYQ_MAX_BATCH];
+  float* y[POLYQ_MAX_BATCH];
+  int64_t count[POLYQ_MAX_BATCH];
+  int32_t splits;
+};
+
+__global__ __launch_bounds__(256) void sum_splits_kernel(const SumArgs a) {
+  const float* __restrict__ partial = a.partial[blockIdx.y];
+  float* __restrict__ y = a.y[blockIdx.y];
+  const int64_t count = a.count[blockIdx.y];
   const int64_t i = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * 4;
   if (i >= count) return;
   if ((count & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0) {
-    float4 v = *reinterpret_cast<const float4*>(partial + i);
-    for (int s = 1; s < splits; ++s) {
-      const float4 w = *reinterpret_cast<const float4*>(partial + s * count + i);
-      v.x += w.x;
-      v.y += w.y;
-      v.z += w.z;
-      v.w += w.w;
+    f4 v = *reinterpret_cast<const f4*>(partial + i);
+    constexpr int kAhead = 8;  // loads in flight (one memory round trip for up to nine splits)
+    for (int s0 = 1; s0 < a.splits; s0 += kAhead) {
+      f4 w[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        w[u] = *reinterpret_cast<const f4*>(partial + std::min(s0 + u, a.splits - 1) * count + i);
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (s0 + u < a.splits) v += w[u];
     }
-    *reinterpret_cast<float4*>(y + i) = v;
+    *reinterpret_cast<f4*>(y + i) = v;
   } else {
     for (int64_t j = i; j < count && j < i + 4; ++j) {
       float v = partial[j];
-      for (int s = 1; s < splits; ++s) v += partial[s * count + j];
+      for (int s = 1; s < a.splits; ++s) v += partial[s * count + j];
       y[j] = v;
     }
   }
@@ -659,64 +764,95 @@ size_t permuted_bytes(const polyq_layout& L, int32_t m) {
   return static_cast<size_t>(align_up(static_cast<int64_t>(m) * L.k * 2, 256));
 }
 
-// Work-groups of one linear (two packed tiles each) per K split.
-int64_t tile_groups(const polyq_layout& L, int32_t m) {
-  return static_cast<int64_t>((L.n_tiles + 1) / 2) * ((m + kTokWG - 1) / kTokWG);
+int groups_of(const polyq_layout& L) {
+  int g = 0;
+  for (int i = 0; i < L.nblocks; ++i) g += (L.block[i].len + kGroup - 1) / kGroup;
+  return g;
 }
 
-// K splits of a single-linear launch whose work-groups would leave CUs idle:
-// as many as keep the launch within one round of one work-group per CU (256),
-// at least four groups per split, at most kMaxSplits.
-int plan_splits(const polyq_layout& L, int32_t m, int32_t count) {
-  const int64_t wg = tile_groups(L, m);
-  if (count != 1 || wg >= 200) return 1;
+// Token tiles of a work-group (16 tokens each): the fewest work-groups of at
+// most kMaxNT, then as even as they come.
+int plan_nt(int32_t m, int32_t* m_tiles) {
+  const int tiles = static_cast<int>((static_cast<int64_t>(m) + kTok - 1) / kTok);
+  const int mt = (tiles + kMaxNT - 1) / kMaxNT;
+  const int nt = (tiles + mt - 1) / mt;
+  *m_tiles = (tiles + nt - 1) / nt;
+  return nt;
+}
+
+struct GemmPlan {
+  int64_t region[POLYQ_MAX_BATCH];   // workspace offset of item i's copy x', or -1
+  size_t partial[POLYQ_MAX_BATCH];   // workspace offset of its partial sums (splits > 1)
+  size_t total;
+  int nt, splits;
+  int32_t m_tiles;
+};
+
+// K splits of a launch: as many as keep it within one round of one work-group
+// per CU, with at least four groups each.  More splits add partial sums and the
+// fixed cost of a work-group faster than they add parallel work: 33 tokens
+// through a 13B-class layer take 165, 119, 153 and 145 us when planned for 128,
+// 256, 384 and 512 work-groups (512 tokens: 622, 457, 528, 511), and 143, 148,
+// 146 and 138 us with at least 1, 2, 3 and 4 groups.
+int plan_splits(const polyq_gemv_item* items, int32_t count, int32_t m_tiles) {
+  int64_t wg = 0;
   int groups = 0;
-  for (int i = 0; i < L.nblocks; ++i) groups += (L.block[i].len / kChunk + kChunksPerGroup - 1) / kChunksPerGroup;
+  for (int i = 0; i < count; ++i) {
+    wg += static_cast<int64_t>((items[i].layout->n_tiles + kTilesWG - 1) / kTilesWG) * m_tiles;
+    groups = std::max(groups, groups_of(*items[i].layout));
+  }
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({256 / wg, kMaxSplits, groups / 4})));
 }
 
 // Workspace of a batch: one clustered copy x' = x[:, perm] (times the channel
 // factors of Eq. 8) per distinct (x, perm, factors) of the items with a
-// permutation or factors (region[i] = byte offset of item i's copy, or -1),
-// then the split partial sums of a single-linear launch (at *partial_off).
-polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_t m,
-                             int64_t* region, size_t* partial_off, int* splits, size_t* total) {
+// permutation or factors, then the partial sums of every item (splits > 1).
+polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_t m, GemmPlan* p) {
   if (items == nullptr || count < 1 || m < 1) return POLYQ_ERR_ARG;
   if (count > POLYQ_MAX_BATCH) return POLYQ_ERR_CAPACITY;
   size_t off = 0;
   for (int i = 0; i < count; ++i) {
     if (!layout_is_valid(items[i].layout)) return POLYQ_ERR_ARG;
     if (static_cast<int64_t>(m) * items[i].layout->k * 2 > 0x7FFFFFFFll) return POLYQ_ERR_CAPACITY;
-    region[i] = -1;
+    p->region[i] = -1;
     if (items[i].perm == nullptr && items[i].xscale == nullptr) continue;
     for (int j = 0; j < i; ++j)
-      if (region[j] >= 0 && items[j].perm == items[i].perm && items[j].x == items[i].x &&
+      if (p->region[j] >= 0 && items[j].perm == items[i].perm && items[j].x == items[i].x &&
           items[j].xscale == items[i].xscale && items[j].layout->k == items[i].layout->k) {
-        region[i] = region[j];
+        p->region[i] = p->region[j];
         break;
       }
-    if (region[i] < 0) {
-      region[i] = static_cast<int64_t>(off);
+    if (p->region[i] < 0) {
+      p->region[i] = static_cast<int64_t>(off);
       off += permuted_bytes(*items[i].layout, m);
     }
   }
-  *splits = plan_splits(*items[0].layout, m, count);
-  *partial_off = off;
-  if (*splits > 1)
-    off += static_cast<size_t>(align_up(static_cast<int64_t>(*splits) * m * items[0].layout->n * 4, 256));
-  *total = off;
+  p->nt = plan_nt(m, &p->m_tiles);
+  p->splits = plan_splits(items, count, p->m_tiles);
+  for (int i = 0; i < count; ++i) {
+    p->partial[i] = off;
+    if (p->splits > 1)
+      off += static_cast<size_t>(align_up(static_cast<int64_t>(p->splits) * m * items[i].layout->n * 4, 256));
+  }
+  p->total = off;
   return POLYQ_OK;
+}
+
+template <int NT>
+void launch_gemm(int nt, int64_t wg, const GemmBatchArgs& a, hipStream_t st) {
+  if (nt == NT)
+    hipLaunchKernelGGL(gemm_kernel<NT>, dim3(static_cast<unsigned>(wg)), dim3(kThreads), 0, st, a);
+  else if constexpr (NT < kMaxNT)
+    launch_gemm<NT + 1>(nt, wg, a, st);
 }
 
 }  // namespace
 
 extern "C" size_t polyq_gemm_batch_workspace_bytes(const polyq_gemm_item* items, int32_t count,
                                                    int32_t m) {
-  int64_t region[POLYQ_MAX_BATCH];
-  size_t partial_off = 0, total = 0;
-  int splits = 1;
-  if (plan_gemm_batch(items, count, m, region, &partial_off, &splits, &total) != POLYQ_OK) return 0;
-  return total;
+  GemmPlan p;
+  if (plan_gemm_batch(items, count, m, &p) != POLYQ_OK) return 0;
+  return p.total;
 }
 
 extern "C" size_t polyq_gemm_workspace_bytes(const polyq_layout* layout, int32_t m, int perm_given) {
@@ -728,20 +864,19 @@ extern "C" size_t polyq_gemm_workspace_bytes(const polyq_layout* layout, int32_t
 
 extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t count, int32_t m,
                                          void* workspace, size_t workspace_bytes, void* stream) {
-  int64_t region[POLYQ_MAX_BATCH];
-  size_t need = 0, partial_off = 0;
-  int splits = 1;
-  const polyq_status pst = plan_gemm_batch(items, count, m, region, &partial_off, &splits, &need);
+  GemmPlan p;
+  const polyq_status pst = plan_gemm_batch(items, count, m, &p);
   if (pst != POLYQ_OK) return pst;
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return POLYQ_ERR_CAPACITY;
-  if (need > 0 && reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return POLYQ_ERR_ARG;
+  if (p.total > 0 && (workspace == nullptr || workspace_bytes < p.total)) return POLYQ_ERR_CAPACITY;
+  if (p.total > 0 && reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return POLYQ_ERR_ARG;
+  uint8_t* ws = static_cast<uint8_t*>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
   GemmBatchArgs a;
   memset(&a, 0, sizeof(a));
   a.count = count;
   a.m = m;
-  a.splits = splits;
-  a.m_tiles = (m + kTokWG - 1) / kTokWG;
+  a.splits = p.splits;
+  a.m_tiles = p.m_tiles;
   for (int i = 0; i < count; ++i) {
     const polyq_gemv_item& itm = items[i];
     const polyq_layout& L = *itm.layout;
@@ -756,7 +891,8 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
   int64_t wg = 0;
   for (int i = 0; i < count; ++i) {
     a.wg_begin[i] = static_cast<int32_t>(wg);
-    wg += tile_groups(*items[i].layout, m) * splits;
+    a.item[i].row_blocks = (items[i].layout->n_tiles + kTilesWG - 1) / kTilesWG;
+    wg += static_cast<int64_t>(a.item[i].row_blocks) * p.m_tiles * p.splits;
     if (wg > 0x7FFFFFFF) return POLYQ_ERR_CAPACITY;
   }
   for (int i = count; i <= POLYQ_MAX_BATCH; ++i) a.wg_begin[i] = static_cast<int32_t>(wg);
@@ -765,60 +901,47 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
   ShuffleJob jobs[POLYQ_MAX_BATCH];
   int njobs = 0;
   for (int i = 0; i < count; ++i) {
-    if (region[i] < 0) continue;
+    if (p.region[i] < 0) continue;
     bool first = true;
-    for (int j = 0; j < i; ++j) first = first && region[j] != region[i];
+    for (int j = 0; j < i; ++j) first = first && p.region[j] != p.region[i];
     if (first)
       jobs[njobs++] = ShuffleJob{items[i].perm, items[i].xscale, items[i].x,
-                                 reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(workspace) + region[i]),
-                                 items[i].layout->k, 0};
+                                 reinterpret_cast<uint16_t*>(ws + p.region[i]), items[i].layout->k, 0};
   }
   launch_shuffle(jobs, njobs, m, true, st);
+  SumArgs sum;
+  memset(&sum, 0, sizeof(sum));
+  sum.splits = p.splits;
+  int64_t widest = 0;
   for (int i = 0; i < count; ++i) {
     const polyq_gemv_item& itm = items[i];
     const polyq_layout& L = *itm.layout;
-    const uint16_t* xp = itm.x;
-    if (region[i] >= 0) xp = reinterpret_cast<const uint16_t*>(static_cast<uint8_t*>(workspace) + region[i]);
     GemmItem& g = a.item[i];
+    sum.partial[i] = reinterpret_cast<const float*>(ws + p.partial[i]);
+    sum.y[i] = itm.y;
+    sum.count[i] = static_cast<int64_t>(m) * L.n;
+    widest = std::max(widest, sum.count[i]);
     g.packed = static_cast<const uint8_t*>(itm.packed);
-    g.x = xp;
-    g.y = itm.y;
+    g.x = p.region[i] >= 0 ? reinterpret_cast<const uint16_t*>(ws + p.region[i]) : itm.x;
+    g.y = p.splits > 1 ? reinterpret_cast<float*>(ws + p.partial[i]) : itm.y;
     g.n = L.n;
     g.k = L.k;
     g.nblocks = L.nblocks;
     g.n_tiles = L.n_tiles;
-    g.n_chunks = L.n_chunks;
-    g.y_vec = (L.n % 4 == 0 && reinterpret_cast<uintptr_t>(itm.y) % 16 == 0) ? 1 : 0;
-    for (int b = 0; b < POLYQ_MAX_BLOCKS; ++b) {
-      const bool used = b < L.nblocks;
-      g.bits[b] = used ? L.block[b].bits : 16;
-      g.cb[b] = used ? L.k_begin[b] / kChunk : L.n_chunks;
-      g.ce[b] = used ? (L.k_begin[b] + L.block[b].len) / kChunk : L.n_chunks;
-      g.off[b] = used ? L.block_offset[b] : 0;
-      g.tb[b] = used ? L.tile_bytes[b] : 0;
-      g.rb[b] = used ? L.record_bytes[b] : 0;
+    g.groups = groups_of(L);
+    g.y_vec = (L.n % 4 == 0 && reinterpret_cast<uintptr_t>(g.y) % 16 == 0) ? 1 : 0;
+    for (int b = 0; b < L.nblocks; ++b) {
+      g.bits[b] = L.block[b].bits;
+      g.len[b] = L.block[b].len;
+      g.k0[b] = L.k_begin[b];
+      g.off[b] = static_cast<int32_t>(L.block_offset[b]);
+      g.tb[b] = static_cast<int32_t>(L.tile_bytes[b]);
     }
   }
-  // split s covers groups [G s / S, G (s + 1) / S) of the group sequence
-  {
-    const polyq_layout& L = *items[0].layout;
-    int gstart[POLYQ_MAX_K / POLYQ_GROUP + POLYQ_MAX_BLOCKS];
-    int G = 0;
-    if (splits > 1)
-      for (int b = 0; b < L.nblocks; ++b)
-        for (int c = L.k_begin[b] / kChunk; c < (L.k_begin[b] + L.block[b].len) / kChunk; c += kChunksPerGroup)
-          gstart[G++] = c;
-    for (int sp = 0; sp <= kMaxSplits; ++sp)
-      a.split_chunk[sp] = splits == 1 ? (sp == 0 ? 0 : L.n_chunks)
-                                      : (sp >= splits ? L.n_chunks : gstart[static_cast<int64_t>(G) * sp / splits]);
-    a.partial = splits > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + partial_off) : nullptr;
-  }
-  hipLaunchKernelGGL(gemm_kernel, dim3(static_cast<unsigned>(wg)), dim3(kThreads), 0, st, a);
-  if (splits > 1) {
-    const int64_t n_el = static_cast<int64_t>(m) * items[0].layout->n;
-    hipLaunchKernelGGL(sum_splits_kernel, dim3(static_cast<unsigned>((n_el + 1023) / 1024)), dim3(256), 0, st,
-                       a.partial, items[0].y, splits, n_el);
-  }
+  launch_gemm<1>(p.nt, wg, a, st);
+  if (p.splits > 1)
+    hipLaunchKernelGGL(sum_splits_kernel, dim3(static_cast<unsigned>((widest + 1023) / 1024), count), dim3(256), 0, st,
+                       sum);
   return hipGetLastError() == hipSuccess ? POLYQ_OK : POLYQ_ERR_DEVICE;
 }
 

@@ -299,3 +299,35 @@ def test_gemm_row_gather_past_the_prefetched_passes():
     torch.cuda.synchronize()
     y_ref, bound = oracle_ref(lin, xb)
     assert_parity(y, y_ref, bound, "gemm k=20480")
+
+
+# Every block-end form (1 .. 4 chunks in the last group), two 16-bit groups, and
+# enough groups for K splits that start inside blocks.
+EDGE_BLOCKS = [(2, 544), (3, 320), (4, 608), (8, 256), (16, 160)]
+
+
+@pytest.mark.parametrize("n", [1, 64, 130, 257, 600])
+@pytest.mark.parametrize("m", [1, 16, 17, 33, 48, 80, 81, 112, 128, 129, 250])
+def test_gemm_token_and_row_tile_edges(n, m):
+    """Every kernel instance (1 .. 8 token tiles of 16) at its first and last
+    token count, and work-groups with 1 .. 4 packed tiles (and a tile past the
+    end): fp32 sums of exact products, so the error stays below the worst case
+    of any summation order, (k + groups + splits) roundings of 2^-24 of
+    sum |w_hat x|."""
+    k = sum(ln for _, ln in EDGE_BLOCKS)
+    lin = random_quant_linear(n, k, EDGE_BLOCKS, seed=7000 + n, mode="codes")
+    zz = lin.zeros.clone()
+    zz[n // 2, 2] = 5.5   # one group of one wave takes the hi + lo path
+    lin.zeros = zz
+    pl = packed_linear(lin)
+    x = _xb(m, k, seed=m)
+    y = pl.prefill(x.to(dev()))
+    y2 = pl.prefill(x.to(dev()))
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    y_ref, bound = oracle_ref(lin, x)
+    err = np.abs(np_(y).astype(np.float64) - y_ref)
+    # the non-integer zero point adds one rounding and the hi + lo split, 2^-16 of its products
+    tol = np.full(n, (k + 18 + 32) * 2.0 ** -24)
+    tol[n // 2] += 2.0 ** -16
+    assert np.all(err <= tol * bound)
