@@ -6,6 +6,8 @@
 // layer emits its output directly in a consumer's clustered channel basis.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "codec.h"
 #include "internal.h"
 
@@ -28,42 +30,83 @@ __device__ __forceinline__ int source_row(const int32_t* __restrict__ row_perm, 
   return static_cast<unsigned>(src) < static_cast<unsigned>(n) ? src : -1;
 }
 
-// One thread per (tile, chunk, lane slice): gathers the slice's 4 rows x 8
-// channels from the row-major codes and writes its 4*B bytes.
+// The blocks of a layer, for the one launch that packs them all.
+struct PackArgs {
+  const uint16_t* codes;
+  const uint16_t* scales;
+  const uint16_t* zeros;
+  const int32_t* row_perm;
+  uint8_t* packed;
+  int32_t tile0;  // first tile of the launch
+  int32_t n, k, nblocks, groups_meta, groups;  // groups: of every block, 16 bits included
+  int32_t bits[POLYQ_MAX_BLOCKS], k0[POLYQ_MAX_BLOCKS], len[POLYQ_MAX_BLOCKS];
+  int32_t first[POLYQ_MAX_BLOCKS];   // first group (of `groups`) of each block
+  int32_t gmeta[POLYQ_MAX_BLOCKS];   // its first group in scales / zeros
+  int64_t offset[POLYQ_MAX_BLOCKS], tile_bytes[POLYQ_MAX_BLOCKS], record_bytes[POLYQ_MAX_BLOCKS];
+};
+
+// One lane slice: its 4 rows x 8 channels of the row-major codes, to 4 B bytes.
 template <int B>
-__global__ __launch_bounds__(kThreads) void pack_codes_kernel(
-    const uint16_t* __restrict__ codes, const int32_t* __restrict__ row_perm, int n, int k, int k0,
-    int nch, int n_tiles, int64_t tile_bytes, int64_t record_bytes, uint8_t* __restrict__ region) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<int64_t>(n_tiles) * nch * 64) return;
-  const int lane = static_cast<int>(idx % 64);
-  const int64_t rest = idx / 64;
-  const int t = static_cast<int>(rest % n_tiles), c = static_cast<int>(rest / n_tiles);
+__device__ __forceinline__ void pack_slice(const uint4 (&u)[4], uint32_t* __restrict__ dst) {
   uint16_t q[32];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int R = t * 64 + 16 * r + (lane % 16);
-    const int src = R < n ? source_row(row_perm, R, n) : -1;
-    if (src >= 0) {
-      const uint4 u = *reinterpret_cast<const uint4*>(codes + static_cast<int64_t>(src) * k + k0 +
-                                                      c * 32 + 8 * (lane / 16));
-      const uint32_t wd[4] = {u.x, u.y, u.z, u.w};
+    const uint32_t wd[4] = {u[r].x, u[r].y, u[r].z, u[r].w};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        q[slice_index(r, 2 * j)] = static_cast<uint16_t>(wd[j] & 0xFFFFu);
-        q[slice_index(r, 2 * j + 1)] = static_cast<uint16_t>(wd[j] >> 16);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) q[slice_index(r, j)] = 0;
+    for (int j = 0; j < 4; ++j) {
+      q[slice_index(r, 2 * j)] = static_cast<uint16_t>(wd[j] & 0xFFFFu);
+      q[slice_index(r, 2 * j + 1)] = static_cast<uint16_t>(wd[j] >> 16);
     }
   }
   uint32_t w[B];
   encode_slice<B>(q, w);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(
-      region + slice_offset(tile_bytes, record_bytes, B <= 8 ? kMetaBytes : 0, B, t, c, lane));
 #pragma unroll
   for (int d = 0; d < B; ++d) dst[d] = w[d];
+}
+
+// One work-group per (tile, group record): wave c packs chunk c (a lane slice
+// per lane), and the scales and zero points of the tile's 64 rows are gathered
+// by the first two waves.  Bound by the 2-byte codes read (141 of the 182 MB of
+// a 13824 x 5120 layer).  Groups vary fastest over the grid, so that the 64
+// bytes of a row that a chunk takes and the 64 that the next one takes come from
+// the same 128-byte line at about the same time: with one launch per block and
+// quantity and tiles fastest that layer took 73.6 us; it takes 41.8 (4.3 TB/s).
+__global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs a) {
+  const int g = static_cast<int>(blockIdx.x % static_cast<unsigned>(a.groups));
+  const int t = a.tile0 + static_cast<int>(blockIdx.x / static_cast<unsigned>(a.groups));
+  int b = 0;
+#pragma unroll
+  for (int i = 1; i < POLYQ_MAX_BLOCKS; ++i) b += (i < a.nblocks && g >= a.first[i]) ? 1 : 0;
+  const int gb = g - a.first[b], bits = a.bits[b];
+  const int c = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
+  uint8_t* record = a.packed + a.offset[b] + t * a.tile_bytes[b] + gb * a.record_bytes[b];
+  const int nch = min(kGroup, a.len[b] - gb * kGroup) / kChunk;
+  uint4 u[4];
+  if (c < nch) {
+    const uint16_t* src0 = a.codes + a.k0[b] + gb * kGroup + c * kChunk + 8 * (lane / 16);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int R = t * 64 + 16 * r + (lane % 16);
+      const int src = R < a.n ? source_row(a.row_perm, R, a.n) : -1;
+      u[r] = src >= 0 ? *reinterpret_cast<const uint4*>(src0 + static_cast<int64_t>(src) * a.k) : uint4{0u, 0u, 0u, 0u};
+    }
+  }
+  if (bits <= 8 && c < 2) {  // wave 0: zero points, wave 1: scales
+    const int R = t * 64 + lane;
+    const int src = R < a.n ? source_row(a.row_perm, R, a.n) : -1;
+    const uint16_t* from = c == 0 ? a.zeros : a.scales;
+    const uint16_t v = src >= 0 ? from[static_cast<int64_t>(src) * a.groups_meta + a.gmeta[b] + gb] : 0;
+    reinterpret_cast<uint16_t*>(record)[c == 0 ? meta_z_half(lane) : meta_s_half(lane)] = v;
+  }
+  if (c >= nch) return;
+  uint32_t* dst = reinterpret_cast<uint32_t*>(record + (bits <= 8 ? kMetaBytes : 0) + (c * 64 + lane) * 4 * bits);
+  switch (bits) {
+    case 2: pack_slice<2>(u, dst); break;
+    case 3: pack_slice<3>(u, dst); break;
+    case 4: pack_slice<4>(u, dst); break;
+    case 8: pack_slice<8>(u, dst); break;
+    default: pack_slice<16>(u, dst); break;
+  }
 }
 
 template <int B>
@@ -91,27 +134,6 @@ __global__ __launch_bounds__(kThreads) void unpack_codes_kernel(
     *reinterpret_cast<uint4*>(codes + static_cast<int64_t>(R) * k + k0 + c * 32 + 8 * (lane / 16)) =
         uint4{out[0], out[1], out[2], out[3]};
   }
-}
-
-// One thread per (row, block-local group): scale and zero point into the group's metadata.
-__global__ __launch_bounds__(kThreads) void pack_meta_kernel(
-    const uint16_t* __restrict__ scales, const uint16_t* __restrict__ zeros,
-    const int32_t* __restrict__ row_perm, int n, int G, int g0, int ng, int64_t tile_bytes,
-    int64_t record_bytes, int rows_total, uint8_t* __restrict__ region) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<int64_t>(rows_total) * ng) return;
-  const int R = static_cast<int>(idx % rows_total);
-  const int g = static_cast<int>(idx / rows_total);
-  uint16_t sv = 0, zv = 0;
-  const int src = R < n ? source_row(row_perm, R, n) : -1;
-  if (src >= 0) {
-    const int64_t at = static_cast<int64_t>(src) * G + g0 + g;
-    sv = scales[at];
-    zv = zeros[at];
-  }
-  uint16_t* meta = reinterpret_cast<uint16_t*>(region + (R / 64) * tile_bytes + g * record_bytes);
-  meta[meta_z_half(R % 64)] = zv;
-  meta[meta_s_half(R % 64)] = sv;
 }
 
 __global__ __launch_bounds__(kThreads) void unpack_meta_kernel(
@@ -240,16 +262,6 @@ __global__ __launch_bounds__(256) void shuffle_rows_lds_kernel(const ShuffleArgs
 }
 
 template <int B>
-void launch_pack(const polyq_layout& L, int i, const uint16_t* codes, const int32_t* row_perm,
-                 uint8_t* region, hipStream_t st) {
-  const int nch = L.block[i].len / kChunk;
-  hipLaunchKernelGGL(pack_codes_kernel<B>,
-                     dim3(grid_for(static_cast<int64_t>(L.n_tiles) * nch * 64)), dim3(kThreads), 0,
-                     st, codes, row_perm, L.n, L.k, L.k_begin[i], nch, L.n_tiles, L.tile_bytes[i],
-                     L.record_bytes[i], region);
-}
-
-template <int B>
 void launch_unpack(const polyq_layout& L, int i, const uint8_t* region, uint16_t* codes,
                    hipStream_t st) {
   const int nch = L.block[i].len / kChunk;
@@ -300,24 +312,34 @@ polyq_status pack_impl(const polyq_layout* layout, const uint16_t* codes, const 
   if (reinterpret_cast<uintptr_t>(packed) % 256 != 0 || reinterpret_cast<uintptr_t>(codes) % 16 != 0)
     return POLYQ_ERR_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  uint8_t* base = static_cast<uint8_t*>(packed);
-  const int rows_total = L.n_tiles * kTileRows;
+  PackArgs a{};
+  a.codes = codes;
+  a.scales = scales;
+  a.zeros = zeros;
+  a.row_perm = row_perm;
+  a.packed = static_cast<uint8_t*>(packed);
+  a.n = L.n;
+  a.k = L.k;
+  a.nblocks = L.nblocks;
+  a.groups_meta = L.n_groups;
   for (int i = 0; i < L.nblocks; ++i) {
-    uint8_t* region = base + L.block_offset[i];
-    switch (L.block[i].bits) {
-      case 2: launch_pack<2>(L, i, codes, row_perm, region, st); break;
-      case 3: launch_pack<3>(L, i, codes, row_perm, region, st); break;
-      case 4: launch_pack<4>(L, i, codes, row_perm, region, st); break;
-      case 8: launch_pack<8>(L, i, codes, row_perm, region, st); break;
-      case 16: launch_pack<16>(L, i, codes, row_perm, region, st); break;
-      default: return POLYQ_ERR_BITS;
-    }
-    if (L.block[i].bits <= 8) {
-      const int ng = (L.block[i].len + kGroup - 1) / kGroup;
-      hipLaunchKernelGGL(pack_meta_kernel, dim3(grid_for(static_cast<int64_t>(rows_total) * ng)),
-                         dim3(kThreads), 0, st, scales, zeros, row_perm, L.n, L.n_groups, L.group_begin[i],
-                         ng, L.tile_bytes[i], L.record_bytes[i], rows_total, region);
-    }
+    a.bits[i] = L.block[i].bits;
+    a.k0[i] = L.k_begin[i];
+    a.len[i] = L.block[i].len;
+    a.first[i] = a.groups;
+    a.gmeta[i] = L.group_begin[i];
+    a.offset[i] = L.block_offset[i];
+    a.tile_bytes[i] = L.tile_bytes[i];
+    a.record_bytes[i] = L.record_bytes[i];
+    a.groups += (L.block[i].len + kGroup - 1) / kGroup;
+  }
+  // a launch's grid counts threads in 32 bits: tiles in as many launches as that takes
+  const int64_t most = ((static_cast<int64_t>(1) << 32) - 1) / kThreads / a.groups;
+  for (int64_t t0 = 0; t0 < L.n_tiles; t0 += most) {
+    const int64_t tiles = std::min<int64_t>(most, L.n_tiles - t0);
+    PackArgs part = a;
+    part.tile0 = static_cast<int32_t>(t0);
+    hipLaunchKernelGGL(pack_kernel, dim3(static_cast<unsigned>(tiles * a.groups)), dim3(kThreads), 0, st, part);
   }
   return hipGetLastError() == hipSuccess ? POLYQ_OK : POLYQ_ERR_DEVICE;
 }
