@@ -57,21 +57,21 @@ struct GemvItem {
   float* partial;     // [S][m][n_tiles * 64], only when S > 1
   uint32_t* counter;  // [n_tiles], only when S > 1
   const uint16_t* xscale;  // fp16 [k] factors on x' (one token only), or NULL
-  int32_t n, k, m, nblocks, S;
+  int32_t n, k, m, waves_total, S;  // waves_total: waves of a tile with a range (the others idle)
   int32_t wave_lds;       // LDS bytes of one wave's staging region
-  int32_t n_tiles, n_chunks;
-  uint32_t tiles_magic;   // div_magic(n_tiles)
+  int32_t n_tiles;
   int32_t zero_offset;    // LDS offset of the work-group's zero row
+  int32_t pad[2];
   int32_t bits[POLYQ_MAX_BLOCKS];
   int32_t chunk_begin[POLYQ_MAX_BLOCKS];
-  int32_t wave_begin[POLYQ_MAX_BLOCKS];  // first wave (per tile) of each block
-  int32_t waves[POLYQ_MAX_BLOCKS];       // waves per tile given to each block
-  uint32_t magic[POLYQ_MAX_BLOCKS];      // div_magic(waves)
+  int32_t chunks[POLYQ_MAX_BLOCKS];
+  int32_t wave_begin[POLYQ_MAX_BLOCKS];  // first wave (per tile) of each block; INT32_MAX past the last
+  int32_t share[POLYQ_MAX_BLOCKS];       // groups per wave: quotient << 16 | remainder (share_begin)
   int32_t tile_bytes[POLYQ_MAX_BLOCKS];
   int64_t block_offset[POLYQ_MAX_BLOCKS];
 };
 
-// The launch: work-group (x, y) runs linear y; x = s * n_tiles + tile.
+// The launch: work-group (x, y, z) runs tile x, split z of linear y.
 struct GemvBatchArgs {
   GemvItem item[kMaxItems];
 };
@@ -439,34 +439,6 @@ __device__ __forceinline__ T kfield(uint32_t kv, int dw) {
 }
 #define ITEM(T, field) kfield<T>(kv, offsetof(GemvItem, field) / 4)
 
-// Block descriptors of the work-group's linear, read from the per-lane copy of
-// its argument record with v_readlane at a uniform (possibly run-time) index:
-// no dependent loads, and no indexed private array for the compiler to spill
-// to scratch memory.
-struct Blocks {
-  uint32_t kv;
-  int nblocks, n_chunks;
-  __device__ int bits(int i) const { return kfield<int32_t>(kv, offsetof(GemvItem, bits) / 4 + i); }
-  __device__ int cb(int i) const { return kfield<int32_t>(kv, offsetof(GemvItem, chunk_begin) / 4 + i); }
-  // a block ends where the next one begins (i + 1 must be a compile-time index
-  // or uniform; reads past the last block fall back to the layer end)
-  __device__ int ce(int i) const {
-    return i + 1 < nblocks ? kfield<int32_t>(kv, offsetof(GemvItem, chunk_begin) / 4 + i + 1) : n_chunks;
-  }
-  __device__ int64_t off(int i) const {
-    return kfield<int64_t>(kv, offsetof(GemvItem, block_offset) / 4 + 2 * i);
-  }
-  __device__ int tb(int i) const { return kfield<int32_t>(kv, offsetof(GemvItem, tile_bytes) / 4 + i); }
-  // record of a group: 256 bytes of metadata (b <= 8) + 4 chunk slices of 256 b bytes
-  __device__ int rb(int i) const {
-    const int b = bits(i);
-    return (b <= 8 ? kMetaBytes : 0) + kChunksPerGroup * 64 * 4 * b;
-  }
-  __device__ int w0(int i) const { return kfield<int32_t>(kv, offsetof(GemvItem, wave_begin) / 4 + i); }
-  __device__ int nw(int i) const { return kfield<int32_t>(kv, offsetof(GemvItem, waves) / 4 + i); }
-  __device__ uint32_t magic(int i) const { return kfield<uint32_t>(kv, offsetof(GemvItem, magic) / 4 + i); }
-};
-
 __device__ __forceinline__ size_t align16(size_t v) { return (v + 15) & ~static_cast<size_t>(15); }
 
 // Global-address-space view of a device pointer.  Pointers rebuilt from the
@@ -501,19 +473,27 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
   static_assert(sizeof(GemvItem) == 256 && offsetof(GemvBatchArgs, item) == 0, "argument layout");
   const uint32_t kv = kargs[blockIdx.y * 64 + lane];
   const int n_tiles = ITEM(int32_t, n_tiles), S = ITEM(int32_t, S);
-  const int local = blockIdx.x;
-  const int s = static_cast<int>(
-      div_by_magic(static_cast<uint32_t>(local), ITEM(uint32_t, tiles_magic), static_cast<uint32_t>(n_tiles)));
-  if (s >= S) return;  // this linear has fewer work-groups than the launch's widest
-  const int tile = local - s * n_tiles;
-  const int m = ITEM(int32_t, m), nblocks = ITEM(int32_t, nblocks), n_chunks = ITEM(int32_t, n_chunks);
-  const Blocks bd{kv, nblocks, n_chunks};
-  // this wave's chunks [c0, c1): one block's share (wave_range)
-  int c0, c1, first;
-  wave_range(__builtin_amdgcn_readfirstlane(s * kWaves + wave), nblocks, n_chunks, bd, &c0, &c1, &first);
-  c0 = __builtin_amdgcn_readfirstlane(c0);
-  c1 = __builtin_amdgcn_readfirstlane(c1);
-  first = __builtin_amdgcn_readfirstlane(first);
+  const int tile = blockIdx.x, s = blockIdx.z;
+  if (s >= S || tile >= n_tiles) return;  // this linear has fewer work-groups than the launch's widest
+  const int m = ITEM(int32_t, m);
+  // This wave's chunks [fl0, fl1) of block `first`: the block whose first wave
+  // is the last one not past w (a compare of all lanes with the record's
+  // wave_begin), then its share.  Few instructions and no branch: each wave runs
+  // this chain alone before its first load (with the launch's flat index divided
+  // back and the blocks searched one by one it took about 1 us of every launch).
+  const int w = __builtin_amdgcn_readfirstlane(s * kWaves + wave);
+  constexpr int kWaveBegin = offsetof(GemvItem, wave_begin) / 4;
+  const uint64_t reached = __ballot(static_cast<int32_t>(kv) <= w) >> kWaveBegin;
+  const int first = __builtin_popcount(static_cast<uint32_t>(reached) & ((1u << POLYQ_MAX_BLOCKS) - 1u)) - 1;
+  auto block_field = [&](size_t offset) { return kfield<int32_t>(kv, static_cast<int>(offset / 4) + first); };
+  const int fb = block_field(offsetof(GemvItem, bits)), fcb = block_field(offsetof(GemvItem, chunk_begin));
+  const int fnch = block_field(offsetof(GemvItem, chunks)), ftb = block_field(offsetof(GemvItem, tile_bytes));
+  const int share = block_field(offsetof(GemvItem, share)), j0 = w - block_field(offsetof(GemvItem, wave_begin));
+  const bool has_work = w < ITEM(int32_t, waves_total);
+  const int g0 = share_begin(share >> 16, share & 0xFFFF, j0), g1 = share_begin(share >> 16, share & 0xFFFF, j0 + 1);
+  const int fl0 = has_work ? kChunksPerGroup * g0 : 0, fl1 = has_work ? min(kChunksPerGroup * g1, fnch) : 0;
+  // record of a group: 256 bytes of metadata (b <= 8) + 4 chunk slices of 256 b bytes
+  const int frb = (fb <= 8 ? kMetaBytes : 0) + kChunksPerGroup * 64 * 4 * fb;
   const uint8_t* packed = ITEM(const uint8_t*, packed);
   const int32_t* perm = ITEM(const int32_t*, perm);
   const uint16_t* xg = ITEM(const uint16_t*, x);
@@ -525,12 +505,8 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
   // flight.  Each wave stages only its own channels: the waves of a
   // work-group share no x', so no work-group barrier is needed before the
   // main loop.
-  const bool has_work = c0 < c1 && first >= 0;
-  const int fb = has_work ? bd.bits(first) : 16, fcb = has_work ? bd.cb(first) : 0;
-  const int fl0 = c0 - fcb, fl1 = has_work ? c1 - fcb : 0;
-  const int frb = has_work ? bd.rb(first) : 0;
-  const int ftb = has_work ? bd.tb(first) : 0;
-  const uint8_t* ftile = has_work ? packed + bd.off(first) + static_cast<int64_t>(tile) * ftb : packed;
+  const uint8_t* ftile = packed + kfield<int64_t>(kv, offsetof(GemvItem, block_offset) / 4 + 2 * first) +
+                         static_cast<int64_t>(tile) * ftb;
   // The block's slice offset, formed before any staging load is issued (an
   // opaque value the compiler keeps live: rematerialized later, it would land
   // in a register with a pending load and cost a full wait).
@@ -541,10 +517,10 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
   // metadata.  The MFMA columns of absent tokens read the work-group's zero
   // row, which every wave fills for the length of its own range (the same
   // zeros: no barrier needed before its reads).
-  const int range = has_work ? (c1 - c0) * kChunk : 0;
+  const int range = (fl1 - fl0) * kChunk;
   // first channel of the range (0 for a wave without work, whose index loads
   // must still stay inside the permutation array)
-  const int kbase = has_work ? c0 * kChunk : 0;
+  const int kbase = has_work ? (fcb + fl0) * kChunk : 0;
   uint16_t* xs16 = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(smem) +
                                                static_cast<size_t>(wave) * ITEM(int32_t, wave_lds));
   uint8_t* wmeta = reinterpret_cast<uint8_t*>(xs16) + align16(m * range * 2);
@@ -784,7 +760,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
     // this lane's activation fragment of block-local chunk 0 (token lane%16,
     // or the zero row; channel quarter lane/16), relative to the staged range
     const uint32_t* xlane = reinterpret_cast<const uint32_t*>(tok < m ? xs16 + tok * range : zs16) +
-                            4 * (lane >> 4) + (fcb - c0) * 16;
+                            4 * (lane >> 4) - fl0 * 16;
     // metadata of block-local group 0 (only groups >= fl0 / 4 are read)
     const uint8_t* meta = wmeta - fg0 * kMetaBytes;
     auto run = [&](auto fixed_tag) {
@@ -1057,7 +1033,7 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   GemvBatchArgs a;
   memset(&a, 0, sizeof(a));
-  int wgs = 0;
+  int tiles = 0, splits = 0;
   for (int i = 0; i < count; ++i) {
     const polyq_gemv_item& t = items[i];
     const polyq_layout& L = *t.layout;
@@ -1079,26 +1055,27 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
     g.n = L.n;
     g.k = L.k;
     g.m = m;
-    g.nblocks = L.nblocks;
     g.S = p.S;
     g.wave_lds = static_cast<int32_t>(gemv_wave_lds_bytes(p, m));
     g.zero_offset = static_cast<int32_t>(gemv_zero_offset(p, m));
     g.n_tiles = L.n_tiles;
-    g.n_chunks = L.n_chunks;
-    g.tiles_magic = div_magic(static_cast<uint32_t>(L.n_tiles));
     int w0 = 0;
     for (int b = 0; b < POLYQ_MAX_BLOCKS; ++b) {
-      const bool used = b < L.nblocks;
-      g.bits[b] = used ? L.block[b].bits : 0;
-      g.chunk_begin[b] = used ? L.k_begin[b] / kChunk : L.n_chunks;
+      g.wave_begin[b] = INT32_MAX;
+      if (b >= L.nblocks) continue;
+      const int nch = L.block[b].len / kChunk, ngr = (nch + kChunksPerGroup - 1) / kChunksPerGroup;
+      g.bits[b] = L.block[b].bits;
+      g.chunk_begin[b] = L.k_begin[b] / kChunk;
+      g.chunks[b] = nch;
       g.wave_begin[b] = w0;
-      g.waves[b] = used ? p.waves[b] : 0;
-      g.magic[b] = div_magic(static_cast<uint32_t>(g.waves[b]));
-      w0 += g.waves[b];
-      g.block_offset[b] = used ? L.block_offset[b] : 0;
-      g.tile_bytes[b] = used ? static_cast<int32_t>(L.tile_bytes[b]) : 0;
+      g.share[b] = (ngr / p.waves[b]) << 16 | (ngr % p.waves[b]);  // ngr <= 8192, waves <= 4096
+      w0 += p.waves[b];
+      g.block_offset[b] = L.block_offset[b];
+      g.tile_bytes[b] = static_cast<int32_t>(L.tile_bytes[b]);
     }
-    wgs = std::max(wgs, L.n_tiles * p.S);
+    g.waves_total = w0;
+    tiles = std::max(tiles, L.n_tiles);
+    splits = std::max(splits, p.S);
   }
   hipStream_t hs = static_cast<hipStream_t>(stream);
   // Eq. 9's explicit shuffle first (with Eq. 8's factors folded in), once per
@@ -1110,7 +1087,7 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
       jobs[njobs++] = ShuffleJob{items[i].perm, items[i].xscale, items[i].x,
                                  reinterpret_cast<uint16_t*>(ws + bp.xp_off[i]), items[i].layout->k, 0};
   launch_shuffle(jobs, njobs, m, false, hs);
-  hipLaunchKernelGGL(gemv_kernel, dim3(wgs, count), dim3(kWaves * 64), bp.lds, hs, a);
+  hipLaunchKernelGGL(gemv_kernel, dim3(tiles, count, splits), dim3(kWaves * 64), bp.lds, hs, a);
   return hipGetLastError() == hipSuccess ? POLYQ_OK : POLYQ_ERR_DEVICE;
 }
 

@@ -29,40 +29,23 @@ struct GemvPlan {
   int32_t lds_groups;               // most group records one wave stages (b <= 8 blocks)
 };
 
-// Exact floor(a / d) for 1 <= d and 0 <= a < 2^31 by a multiply and shifts
-// (round-up multiplier, Granlund and Montgomery 1994): with l = floor(log2 d)
-// and M = ceil(2^(32+l) / d), a M / 2^(32+l) = a / d + a e / (d 2^(32+l)) where
-// e = M d - 2^(32+l) < d < 2^(l+1); since a e < 2^31 2^(l+1) = 2^(32+l) the
-// excess stays below 1/d and cannot reach the next integer.  M < 2^32 unless d
-// is a power of two, where div_magic returns 0 and the quotient is a >> l.
-__host__ __device__ inline int div_log2(uint32_t d) { return d <= 1 ? 0 : 31 - __builtin_clz(d); }
-__host__ __device__ inline uint32_t div_magic(uint32_t d) {
-  if ((d & (d - 1)) == 0) return 0u;  // 0, 1 and powers of two
-  return static_cast<uint32_t>(((1ull << (32 + div_log2(d))) + d - 1) / d);
-}
-__host__ __device__ inline uint32_t div_by_magic(uint32_t a, uint32_t magic, uint32_t d) {
-  const uint32_t hi =
-      magic == 0 ? a : static_cast<uint32_t>((static_cast<uint64_t>(a) * magic) >> 32);
-  return hi >> div_log2(d);
-}
+// A block's groups over its waves: the first r of nw waves take q + 1 groups, the
+// others q (q = groups / nw, r = groups mod nw); the first group of wave j.
+__host__ __device__ inline int share_begin(int q, int r, int j) { return j * q + (j < r ? j : r); }
 
 // Chunk range [lo, hi) of wave w of every tile: waves are handed to the blocks
 // in order (waves[i] to block i, starting at wave w0[i]) and a block's groups
-// are split evenly among its waves, so that every wave starts and ends on a
-// group boundary of one block.  Waves past the last block get an empty range
-// at the end of the layer.  `blk` gives, for block i (a uniform run-time
-// index), cb(i) / ce(i) (chunk range), w0(i), nw(i) and magic(i) =
-// div_magic(nw(i)).  Shared by the host planner and the kernel, which must
-// agree exactly; the kernel evaluates it in scalar registers, so the block is
-// found with a handful of compares and read once.  `block` (optional) receives
-// the block index i (or -1); the range is empty unless w < w0(i) + nw(i).
+// are split evenly among its waves (share_begin), so that every wave starts and
+// ends on a group boundary of one block.  Waves past the last block get an empty
+// range at the end of the layer.  `blk` gives, for block i, cb(i) / ce(i) (chunk
+// range), w0(i) and nw(i).  The host planner's form; the kernel reads the same
+// shares from its argument record.  `block` (optional) receives the block index
+// i (or -1); the range is empty unless w < w0(i) + nw(i).
 template <class Blk>
-__host__ __device__ inline void wave_range(int w, int nblocks, int n_chunks, const Blk& blk,
-                                           int* lo, int* hi, int* block = nullptr) {
+inline void wave_range(int w, int nblocks, int n_chunks, const Blk& blk, int* lo, int* hi, int* block = nullptr) {
   int i = -1;
-#pragma unroll
-  for (int b = 0; b < POLYQ_MAX_BLOCKS; ++b)
-    if (b < nblocks && blk.w0(b) <= w) i = b;
+  for (int b = 0; b < nblocks; ++b)
+    if (blk.w0(b) <= w) i = b;
   *lo = *hi = n_chunks;
   if (block) *block = i;
   if (i < 0) return;
@@ -70,9 +53,8 @@ __host__ __device__ inline void wave_range(int w, int nblocks, int n_chunks, con
   if (w >= w0 + nw) return;
   const int cb = blk.cb(i), nch = blk.ce(i) - cb;
   const int ngr = (nch + kChunksPerGroup - 1) / kChunksPerGroup, j = w - w0;
-  const uint32_t magic = blk.magic(i);
-  const int a = kChunksPerGroup * static_cast<int>(div_by_magic(static_cast<uint32_t>(ngr * j), magic, nw));
-  const int b = kChunksPerGroup * static_cast<int>(div_by_magic(static_cast<uint32_t>(ngr * (j + 1)), magic, nw));
+  const int a = kChunksPerGroup * share_begin(ngr / nw, ngr % nw, j);
+  const int b = kChunksPerGroup * share_begin(ngr / nw, ngr % nw, j + 1);
   *lo = cb + (a < nch ? a : nch);
   *hi = cb + (b < nch ? b : nch);
 }
@@ -132,7 +114,6 @@ struct LayoutBlocks {
     return first;
   }
   int nw(int i) const { return waves[i]; }
-  uint32_t magic(int i) const { return div_magic(static_cast<uint32_t>(waves[i])); }
 };
 
 inline int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
