@@ -770,16 +770,6 @@ int groups_of(const polyq_layout& L) {
   return g;
 }
 
-// Token tiles of a work-group (16 tokens each): the fewest work-groups of at
-// most kMaxNT, then as even as they come.
-int plan_nt(int32_t m, int32_t* m_tiles) {
-  const int tiles = static_cast<int>((static_cast<int64_t>(m) + kTok - 1) / kTok);
-  const int mt = (tiles + kMaxNT - 1) / kMaxNT;
-  const int nt = (tiles + mt - 1) / mt;
-  *m_tiles = (tiles + nt - 1) / nt;
-  return nt;
-}
-
 struct GemmPlan {
   int64_t region[POLYQ_MAX_BATCH];   // workspace offset of item i's copy x', or -1
   size_t partial[POLYQ_MAX_BATCH];   // workspace offset of its partial sums (splits > 1)
@@ -788,20 +778,42 @@ struct GemmPlan {
   int32_t m_tiles;
 };
 
-// K splits of a launch: as many as keep it within one round of one work-group
-// per CU, with at least four groups each.  More splits add partial sums and the
-// fixed cost of a work-group faster than they add parallel work: 33 tokens
-// through a 13B-class layer take 165, 119, 153 and 145 us when planned for 128,
-// 256, 384 and 512 work-groups (512 tokens: 622, 457, 528, 511), and 143, 148,
-// 146 and 138 us with at least 1, 2, 3 and 4 groups.
-int plan_splits(const polyq_gemv_item* items, int32_t count, int32_t m_tiles) {
-  int64_t wg = 0;
+// K splits of a launch of `wg` work-groups per split: as many as keep it within
+// one round of one work-group per CU, with at least four groups each.  More
+// splits add partial sums and the fixed cost of a work-group faster than they
+// add parallel work: 33 tokens through a 13B-class layer take 165, 119, 153 and
+// 145 us when planned for 128, 256, 384 and 512 work-groups (512 tokens: 622,
+// 457, 528, 511), and 143, 148, 146 and 138 us with at least 1, 2, 3 and 4
+// groups.
+int64_t splits_for(int64_t wg, int groups) {
+  return std::max<int64_t>(1, std::min<int64_t>({256 / wg, kMaxSplits, groups / 4}));
+}
+
+// Token tiles of a work-group (nt, 16 tokens each) and K splits: the least
+// estimated time, rounds of 256 work-groups x (11 + nt) / splits.  A group takes
+// a work-group about (11 + nt) units (1.9 us at 3 tiles, 2.6 us at 8): mostly the
+// chain that does not depend on the tokens, so the largest nt wins unless a
+// smaller one fills a round that would leave CUs idle: 512 tokens x 10240 rows x
+// 5120 channels take 86 us at nt = 6 (240 work-groups) and 97 at 8 (160), 77
+// tokens x 1357 rows x 2976 channels 20.6 at 1 and 28.0 at 5.  Ties: the larger.
+void plan_shape(const polyq_gemv_item* items, int32_t count, int32_t m, int* nt, int32_t* m_tiles, int* splits) {
+  const int64_t tiles = (static_cast<int64_t>(m) + kTok - 1) / kTok;
+  int64_t rows = 0;
   int groups = 0;
   for (int i = 0; i < count; ++i) {
-    wg += static_cast<int64_t>((items[i].layout->n_tiles + kTilesWG - 1) / kTilesWG) * m_tiles;
+    rows += (items[i].layout->n_tiles + kTilesWG - 1) / kTilesWG;
     groups = std::max(groups, groups_of(*items[i].layout));
   }
-  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({256 / wg, kMaxSplits, groups / 4})));
+  double best = 0;
+  for (int t = static_cast<int>(std::min<int64_t>(kMaxNT, tiles)); t >= 1; --t) {
+    const int64_t mt = (tiles + t - 1) / t, s = splits_for(rows * mt, groups);
+    const double cost = static_cast<double>((rows * mt * s + 255) / 256) * (11 + t) / static_cast<double>(s);
+    if (best != 0 && cost >= best) continue;
+    best = cost;
+    *nt = t;
+    *m_tiles = static_cast<int32_t>(mt);
+    *splits = static_cast<int>(s);
+  }
 }
 
 // Workspace of a batch: one clustered copy x' = x[:, perm] (times the channel
@@ -827,8 +839,7 @@ polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_
       off += permuted_bytes(*items[i].layout, m);
     }
   }
-  p->nt = plan_nt(m, &p->m_tiles);
-  p->splits = plan_splits(items, count, p->m_tiles);
+  plan_shape(items, count, m, &p->nt, &p->m_tiles, &p->splits);
   for (int i = 0; i < count; ++i) {
     p->partial[i] = off;
     if (p->splits > 1)

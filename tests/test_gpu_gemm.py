@@ -331,3 +331,32 @@ def test_gemm_token_and_row_tile_edges(n, m):
     tol = np.full(n, (k + 18 + 32) * 2.0 ** -24)
     tol[n // 2] += 2.0 ** -16
     assert np.all(err <= tol * bound)
+
+
+@pytest.fixture(scope="module")
+def tall():
+    """65536 rows: 256 row blocks, so a launch is one round at one work-group per
+    row block and the plan takes every token tile of the prompt into it."""
+    blocks = [(2, 160), (3, 96), (4, 128), (8, 96), (16, 160)]
+    lin = random_quant_linear(65536, 640, blocks, seed=8100, mode="codes")
+    zz = lin.zeros.clone()
+    zz[33000, 1] = 5.5
+    lin.zeros = zz
+    return lin, packed_linear(lin)
+
+
+@pytest.mark.parametrize("m", [16, 17, 33, 64, 65, 96, 97, 128, 129])
+def test_gemm_every_token_tile_count(tall, m):
+    """The kernel instances of 1 .. 8 token tiles (and of two work-groups per row
+    block) at full size, on sampled rows of every wave and the rows around a
+    non-integer zero point: the bound of test_gemm_token_and_row_tile_edges."""
+    lin, pl = tall
+    x = _xb(m, lin.k, seed=m)
+    y = pl.prefill(x.to(dev()))
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(0, 256, 5), np.arange(32992, 33008), np.arange(65400, 65536, 7)]))
+    y_ref, bound = oracle_ref(lin, x, rows=rows)
+    err = np.abs(np_(y)[:, rows].astype(np.float64) - y_ref)
+    tol = np.full(len(rows), (lin.k + 18 + 32) * 2.0 ** -24)
+    tol[rows == 33000] += 2.0 ** -16
+    assert np.all(err <= tol * bound)
