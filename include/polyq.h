@@ -304,11 +304,15 @@ polyq_status polyq_gemm(const polyq_layout* layout, const void* packed, const in
  * what polyq_gemm(items[i].layout, items[i].packed, items[i].perm, items[i].x,
  * m, items[i].y, ...) computes, with the same argument rules per item (x holds
  * bf16 bits here).  Items with the same x and perm share one permuted copy.
- *   workspace: at least polyq_gemm_batch_workspace_bytes(items, count, m)
- *   bytes of device scratch (the permuted copies, and the split partial sums
- *   of every item as in polyq_gemm); contents on entry are ignored.  The
- *   query reads the layout, x and perm fields; 0 on an invalid request or
- *   when no scratch is needed.
+ *   workspace: polyq_gemm_batch_workspace_bytes(items, count, m) bytes of
+ *   device scratch, 16-byte aligned (the permuted copies, and the split
+ *   partial sums of every item as in polyq_gemm); contents on entry are
+ *   ignored.  The query reads the layout, x, perm and xscale fields; 0 on an
+ *   invalid request or when no scratch is needed.  With count == 1 less is
+ *   refused.  With count > 1 the permuted copies alone are required (each
+ *   m * k * 2 bytes rounded up to 256; none for items with neither a
+ *   permutation nor factors: then NULL does): K is split only as far as the
+ *   partial sums fit, and a short prompt takes longer without.
  */
 typedef polyq_gemv_item polyq_gemm_item;
 

@@ -785,8 +785,8 @@ struct GemmPlan {
 // 145 us when planned for 128, 256, 384 and 512 work-groups (512 tokens: 622,
 // 457, 528, 511), and 143, 148, 146 and 138 us with at least 1, 2, 3 and 4
 // groups.
-int64_t splits_for(int64_t wg, int groups) {
-  return std::max<int64_t>(1, std::min<int64_t>({256 / wg, kMaxSplits, groups / 4}));
+int64_t splits_for(int64_t wg, int groups, int most) {
+  return std::max<int64_t>(1, std::min<int64_t>({256 / wg, most, groups / 4}));
 }
 
 // Token tiles of a work-group (nt, 16 tokens each) and K splits: the least
@@ -796,7 +796,8 @@ int64_t splits_for(int64_t wg, int groups) {
 // smaller one fills a round that would leave CUs idle: 512 tokens x 10240 rows x
 // 5120 channels take 86 us at nt = 6 (240 work-groups) and 97 at 8 (160), 77
 // tokens x 1357 rows x 2976 channels 20.6 at 1 and 28.0 at 5.  Ties: the larger.
-void plan_shape(const polyq_gemv_item* items, int32_t count, int32_t m, int* nt, int32_t* m_tiles, int* splits) {
+void plan_shape(const polyq_gemv_item* items, int32_t count, int32_t m, int most_splits, int* nt, int32_t* m_tiles,
+                int* splits) {
   const int64_t tiles = (static_cast<int64_t>(m) + kTok - 1) / kTok;
   int64_t rows = 0;
   int groups = 0;
@@ -806,7 +807,7 @@ void plan_shape(const polyq_gemv_item* items, int32_t count, int32_t m, int* nt,
   }
   double best = 0;
   for (int t = static_cast<int>(std::min<int64_t>(kMaxNT, tiles)); t >= 1; --t) {
-    const int64_t mt = (tiles + t - 1) / t, s = splits_for(rows * mt, groups);
+    const int64_t mt = (tiles + t - 1) / t, s = splits_for(rows * mt, groups, most_splits);
     const double cost = static_cast<double>((rows * mt * s + 255) / 256) * (11 + t) / static_cast<double>(s);
     if (best != 0 && cost >= best) continue;
     best = cost;
@@ -819,7 +820,10 @@ void plan_shape(const polyq_gemv_item* items, int32_t count, int32_t m, int* nt,
 // Workspace of a batch: one clustered copy x' = x[:, perm] (times the channel
 // factors of Eq. 8) per distinct (x, perm, factors) of the items with a
 // permutation or factors, then the partial sums of every item (splits > 1).
-polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_t m, GemmPlan* p) {
+// A batch (count > 1) is planned with the splits whose partial sums fit `room`
+// bytes (one always does: it needs the copies alone); a single linear always
+// with its own plan, which the caller's workspace has to hold.
+polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_t m, size_t room, GemmPlan* p) {
   if (items == nullptr || count < 1 || m < 1) return POLYQ_ERR_ARG;
   if (count > POLYQ_MAX_BATCH) return POLYQ_ERR_CAPACITY;
   size_t off = 0;
@@ -839,11 +843,19 @@ polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_
       off += permuted_bytes(*items[i].layout, m);
     }
   }
-  plan_shape(items, count, m, &p->nt, &p->m_tiles, &p->splits);
+  auto partial_bytes = [&](int i, int splits) {
+    return static_cast<size_t>(align_up(static_cast<int64_t>(splits) * m * items[i].layout->n * 4, 256));
+  };
+  int most = kMaxSplits;
+  for (; count > 1 && most > 1; --most) {
+    size_t need = off;
+    for (int i = 0; i < count; ++i) need += partial_bytes(i, most);
+    if (need <= room) break;
+  }
+  plan_shape(items, count, m, most, &p->nt, &p->m_tiles, &p->splits);
   for (int i = 0; i < count; ++i) {
     p->partial[i] = off;
-    if (p->splits > 1)
-      off += static_cast<size_t>(align_up(static_cast<int64_t>(p->splits) * m * items[i].layout->n * 4, 256));
+    if (p->splits > 1) off += partial_bytes(i, p->splits);
   }
   p->total = off;
   return POLYQ_OK;
@@ -862,7 +874,7 @@ void launch_gemm(int nt, int64_t wg, const GemmBatchArgs& a, hipStream_t st) {
 extern "C" size_t polyq_gemm_batch_workspace_bytes(const polyq_gemm_item* items, int32_t count,
                                                    int32_t m) {
   GemmPlan p;
-  if (plan_gemm_batch(items, count, m, &p) != POLYQ_OK) return 0;
+  if (plan_gemm_batch(items, count, m, SIZE_MAX, &p) != POLYQ_OK) return 0;
   return p.total;
 }
 
@@ -876,7 +888,8 @@ extern "C" size_t polyq_gemm_workspace_bytes(const polyq_layout* layout, int32_t
 extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t count, int32_t m,
                                          void* workspace, size_t workspace_bytes, void* stream) {
   GemmPlan p;
-  const polyq_status pst = plan_gemm_batch(items, count, m, &p);
+  const size_t room = reinterpret_cast<uintptr_t>(workspace) % 16 == 0 && workspace != nullptr ? workspace_bytes : 0;
+  const polyq_status pst = plan_gemm_batch(items, count, m, room, &p);
   if (pst != POLYQ_OK) return pst;
   if (p.total > 0 && (workspace == nullptr || workspace_bytes < p.total)) return POLYQ_ERR_CAPACITY;
   if (p.total > 0 && reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return POLYQ_ERR_ARG;

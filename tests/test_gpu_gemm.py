@@ -1,4 +1,6 @@
 """Prefill GEMM (bf16 MFMA, fp32 accumulation) on the GPU against the fp64 oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -360,3 +362,42 @@ def test_gemm_every_token_tile_count(tall, m):
     tol = np.full(len(rows), (lin.k + 18 + 32) * 2.0 ** -24)
     tol[rows == 33000] += 2.0 ** -16
     assert np.all(err <= tol * bound)
+
+
+@pytest.mark.parametrize("clustered", [True, False])
+def test_gemm_batch_runs_in_the_room_of_its_copies(clustered):
+    """A batch needs only the permuted copies: with less than the query it splits
+    K as far as the partial sums fit (not at all without room), with the same
+    parity; a single linear keeps its queried size.  18 groups and 33 tokens:
+    the full plan splits K four ways."""
+    blocks = [(2, 992), (3, 704), (4, 256), (8, 64), (16, 32)]
+    k, m, ns = 2048, 33, (320, 130)
+    lins = [random_quant_linear(n, k, blocks, seed=610 + i, mode="gauss") for i, n in enumerate(ns)]
+    lins[1].perm = lins[0].perm
+    pls = [packed_linear(lin) for lin in lins]
+    x = _xb(m, k, seed=61)
+    xd = x.to(dev())
+    perm = None if clustered else pls[0].perm
+    given = pls[0].permute(xd) if clustered else xd
+    ys = [torch.empty((m, n), device=dev()) for n in ns]
+    arr = (pq._lib.GemvItem * 2)(*[pq._lib.GemvItem(ctypes.pointer(pl.layout), pl.packed.data_ptr(), pq._lib._ptr(perm),
+                                                    given.data_ptr(), y.data_ptr(), None) for pl, y in zip(pls, ys)])
+    lib, copies = pq.lib(), 0 if clustered else m * k * 2
+    full = lib.polyq_gemm_batch_workspace_bytes(arr, 2, m)
+    partial = sum(-(-m * n * 4 // 256) * 256 for n in ns)
+    assert copies % 256 == 0 and full > copies + 2 * partial
+    ws = torch.empty(full, dtype=torch.uint8, device=dev())
+    for room, at in [(copies, 0), (copies + 2 * partial, 0), (full - 1, 0), (full, 0)] + [(full - 4, 4)] * clustered:
+        for y in ys:
+            y.fill_(float("nan"))
+        ptr = ws.data_ptr() + at if room else None
+        assert lib.polyq_gemm_batch(arr, 2, m, ptr, room, None) == 0, (room, at)
+        torch.cuda.synchronize()
+        for lin, y in zip(lins, ys):
+            y_ref, bound = oracle_ref(lin, x)
+            assert_parity(y, y_ref, bound, f"gemm batch in {room} of {full} bytes n={lin.n}")
+    if not clustered:
+        assert lib.polyq_gemm_batch(arr, 2, m, ws.data_ptr(), copies - 1, None) == 5   # POLYQ_ERR_CAPACITY
+        assert lib.polyq_gemm_batch(arr, 2, m, ws.data_ptr() + 4, full - 4, None) == 1  # POLYQ_ERR_ARG
+    one = lib.polyq_gemm_batch_workspace_bytes(arr, 1, m)
+    assert one > copies and lib.polyq_gemm_batch(arr, 1, m, ws.data_ptr(), one - 1, None) == 5
