@@ -61,7 +61,8 @@ struct GemvItem {
   int32_t wave_lds;       // LDS bytes of one wave's staging region
   int32_t n_tiles;
   int32_t zero_offset;    // LDS offset of the work-group's zero row
-  int32_t pad[2];
+  uint32_t tiles_magic;   // div_magic(n_tiles)
+  int32_t pad;
   int32_t bits[POLYQ_MAX_BLOCKS];
   int32_t chunk_begin[POLYQ_MAX_BLOCKS];
   int32_t chunks[POLYQ_MAX_BLOCKS];
@@ -71,7 +72,7 @@ struct GemvItem {
   int64_t block_offset[POLYQ_MAX_BLOCKS];
 };
 
-// The launch: work-group (x, y, z) runs tile x, split z of linear y.
+// The launch: work-group (x, y, z) runs a tile and split of linear y (gemv_place).
 struct GemvBatchArgs {
   GemvItem item[kMaxItems];
 };
@@ -473,14 +474,14 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
   static_assert(sizeof(GemvItem) == 256 && offsetof(GemvBatchArgs, item) == 0, "argument layout");
   const uint32_t kv = kargs[blockIdx.y * 64 + lane];
   const int n_tiles = ITEM(int32_t, n_tiles), S = ITEM(int32_t, S);
-  const int tile = blockIdx.x, s = blockIdx.z;
-  if (s >= S || tile >= n_tiles) return;  // this linear has fewer work-groups than the launch's widest
+  int tile, s;
+  gemv_place(blockIdx.x, blockIdx.z, ITEM(uint32_t, tiles_magic), n_tiles, &tile, &s);
+  if (s >= S) return;  // this linear has fewer work-groups than the launch's widest
   const int m = ITEM(int32_t, m);
   // This wave's chunks [fl0, fl1) of block `first`: the block whose first wave
   // is the last one not past w (a compare of all lanes with the record's
   // wave_begin), then its share.  Few instructions and no branch: each wave runs
-  // this chain alone before its first load (with the launch's flat index divided
-  // back and the blocks searched one by one it took about 1 us of every launch).
+  // this chain alone before its first load.
   const int w = __builtin_amdgcn_readfirstlane(s * kWaves + wave);
   constexpr int kWaveBegin = offsetof(GemvItem, wave_begin) / 4;
   const uint64_t reached = __ballot(static_cast<int32_t>(kv) <= w) >> kWaveBegin;
@@ -1033,7 +1034,7 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   GemvBatchArgs a;
   memset(&a, 0, sizeof(a));
-  int tiles = 0, splits = 0;
+  int32_t tiles[POLYQ_MAX_BATCH], splits[POLYQ_MAX_BATCH];
   for (int i = 0; i < count; ++i) {
     const polyq_gemv_item& t = items[i];
     const polyq_layout& L = *t.layout;
@@ -1059,6 +1060,7 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
     g.wave_lds = static_cast<int32_t>(gemv_wave_lds_bytes(p, m));
     g.zero_offset = static_cast<int32_t>(gemv_zero_offset(p, m));
     g.n_tiles = L.n_tiles;
+    g.tiles_magic = div_magic(static_cast<uint32_t>(L.n_tiles));
     int w0 = 0;
     for (int b = 0; b < POLYQ_MAX_BLOCKS; ++b) {
       g.wave_begin[b] = INT32_MAX;
@@ -1074,8 +1076,8 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
       g.tile_bytes[b] = static_cast<int32_t>(L.tile_bytes[b]);
     }
     g.waves_total = w0;
-    tiles = std::max(tiles, L.n_tiles);
-    splits = std::max(splits, p.S);
+    tiles[i] = L.n_tiles;
+    splits[i] = p.S;
   }
   hipStream_t hs = static_cast<hipStream_t>(stream);
   // Eq. 9's explicit shuffle first (with Eq. 8's factors folded in), once per
@@ -1087,7 +1089,8 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
       jobs[njobs++] = ShuffleJob{items[i].perm, items[i].xscale, items[i].x,
                                  reinterpret_cast<uint16_t*>(ws + bp.xp_off[i]), items[i].layout->k, 0};
   launch_shuffle(jobs, njobs, m, false, hs);
-  hipLaunchKernelGGL(gemv_kernel, dim3(tiles, count, splits), dim3(kWaves * 64), bp.lds, hs, a);
+  const GemvGrid grid = gemv_grid(tiles, splits, count);
+  hipLaunchKernelGGL(gemv_kernel, dim3(grid.x, count, grid.z), dim3(kWaves * 64), bp.lds, hs, a);
   return hipGetLastError() == hipSuccess ? POLYQ_OK : POLYQ_ERR_DEVICE;
 }
 

@@ -20,6 +20,7 @@ constexpr int kMetaBytes = kTileRows * 4;   // {fp16 s, fp16 z} per row of a til
 // chunk range wave_range(w).  Every wave stays inside one block: block i gets
 // waves[i] waves per tile.
 constexpr int kMaxSplitEntries = 4096;  // S * W <= this
+constexpr int kResidentWGs = 768;       // 256 CUs x 3 co-resident 4-wave work-groups (<= 168 VGPRs)
 
 struct GemvPlan {
   int32_t S;                        // WG splits per 64-row tile
@@ -28,6 +29,59 @@ struct GemvPlan {
   int32_t lds_chunks;               // largest chunk range of one wave
   int32_t lds_groups;               // most group records one wave stages (b <= 8 blocks)
 };
+
+// Exact floor(a / d) for 1 <= d and 0 <= a < 2^31 by a multiply and shifts
+// (round-up multiplier, Granlund and Montgomery 1994): with l = floor(log2 d)
+// and M = ceil(2^(32+l) / d), a M / 2^(32+l) = a / d + a e / (d 2^(32+l)) where
+// e = M d - 2^(32+l) < d < 2^(l+1); since a e < 2^31 2^(l+1) = 2^(32+l) the
+// excess stays below 1/d and cannot reach the next integer.  M < 2^32 unless d
+// is a power of two, where div_magic returns 0 and the quotient is a >> l.
+__host__ __device__ inline int div_log2(uint32_t d) { return d <= 1 ? 0 : 31 - __builtin_clz(d); }
+__host__ __device__ inline uint32_t div_magic(uint32_t d) {
+  if ((d & (d - 1)) == 0) return 0u;  // 0, 1 and powers of two
+  return static_cast<uint32_t>(((1ull << (32 + div_log2(d))) + d - 1) / d);
+}
+__host__ __device__ inline uint32_t div_by_magic(uint32_t a, uint32_t magic, uint32_t d) {
+  const uint32_t hi =
+      magic == 0 ? a : static_cast<uint32_t>((static_cast<uint64_t>(a) * magic) >> 32);
+  return hi >> div_log2(d);
+}
+
+// Grid of a decode launch: work-group (x, y, z) runs linear y, tile x mod n_tiles
+// and split x / n_tiles + z of it (gemv_place); splits at or past the linear's
+// own have nothing to do.  Flat (z = 0, x over tiles x splits of the widest
+// linear): a linear's splits are adjacent, and at most `count` times the widest
+// linear's work-groups are launched whatever the others look like.  Split by
+// split (x over the tiles, z over the splits), for linears of equal tiles and
+// splits, where it launches not one more: a CU's work-groups (256 apart) are then
+// of different splits, that is of different bit-widths, which balances a launch
+// that is resident all at once, and one of two rounds or more.  In between, a
+// second round is a mere tail, and the flat order, whose first linear is done with
+// its fix-ups by then, is the faster.  Split by split / flat, one token, 3 bits:
+// q/k/v of 5120 (720 work-groups) 13.0 / 14.3 us, of 8192 (768) 24.9 / 29.7;
+// gate/up of 13824 (864) 20.1 / 19.5, of 14336 (896) 18.1 / 17.0; 6 bits, of 25600
+// (1600) 38.0 / 39.5 (4 tokens 47.9 / 45.3, 16 tokens 74.3 / 76.2).  Unequal
+// linears in one box of the widest of each: 4096 + 2 x 1024 rows 11.1 / 9.3,
+// 131072 rows x 512 with 64 x 65536 (16 tokens) 124 / 49.
+struct GemvGrid {
+  int32_t x, z;
+};
+inline GemvGrid gemv_grid(const int32_t* n_tiles, const int32_t* splits, int count) {
+  bool equal = true;
+  int widest = 0;
+  for (int i = 0; i < count; ++i) {
+    equal = equal && n_tiles[i] == n_tiles[0] && splits[i] == splits[0];
+    widest = widest > n_tiles[i] * splits[i] ? widest : n_tiles[i] * splits[i];
+  }
+  const int64_t total = static_cast<int64_t>(widest) * count;
+  if (equal && (total <= kResidentWGs || total >= 2 * kResidentWGs)) return GemvGrid{n_tiles[0], splits[0]};
+  return GemvGrid{widest, 1};
+}
+__host__ __device__ inline void gemv_place(uint32_t x, uint32_t z, uint32_t magic, int n_tiles, int* tile, int* split) {
+  const int turn = static_cast<int>(div_by_magic(x, magic, static_cast<uint32_t>(n_tiles)));
+  *tile = static_cast<int>(x) - turn * n_tiles;
+  *split = turn + static_cast<int>(z);
+}
 
 // A block's groups over its waves: the first r of nw waves take q + 1 groups, the
 // others q (q = groups / nw, r = groups mod nw); the first group of wave j.

@@ -13,7 +13,6 @@ bool bits_in_palette(int b) { return b == 2 || b == 3 || b == 4 || b == 8 || b =
 
 // GEMV work split knobs.
 constexpr int kWavesPerWG = 4;
-constexpr int kResidentWGs = 768;        // 256 CUs x 3 co-resident 4-wave work-groups (<= 168 VGPRs)
 constexpr int kMinChunksPerWave = 4;      // below this the per-wave setup dominates
 // Per work-group, one token: a third of the CU's 160 KB, so that the three
 // work-groups the VGPR budget allows stay co-resident.

@@ -2,7 +2,8 @@
 // (alloc.cpp): packed layouts of random valid block lists, the statuses of
 // invalid ones, the decode-GEMV work split (every chunk of a layer covered by
 // exactly one wave, each wave inside one block and starting on one of its
-// group boundaries, LDS within the work-group budget), and the allocation's
+// group boundaries, LDS within the work-group budget), the decode grid of a
+// batch, and the allocation's
 // outputs (palette bit-widths, the budget never exceeded by waterfilling,
 // counts on the quantum after matching, a permutation from clustering).
 // Built with g++ and the address and undefined-behaviour sanitizers by
@@ -114,6 +115,52 @@ void check_gemv_plan(const polyq_layout& L, int m, int launch_tiles) {
   CHECK(polyq::gemv_lds_bytes(p, m) <= 80 * 1024, "LDS %zu", polyq::gemv_lds_bytes(p, m));
   const size_t ws = polyq_gemv_workspace_bytes(&L, m);
   CHECK(ws >= polyq::gemv_workspace_for(L, m, p) || launch_tiles != L.n_tiles, "workspace %zu", ws);
+}
+
+// The decode grid of a batch: every tile and split of every linear is reached by
+// exactly one work-group, and no more are launched than `count` times the widest
+// linear's (items of different n and k may not multiply each other's extremes).
+void check_gemv_grid(Rng& r) {
+  const int count = r.uniform(1, POLYQ_MAX_BATCH), m = r.uniform(1, 16);
+  const bool alike = r.next() % 2 != 0;
+  std::vector<polyq_layout> L(count);
+  int launch_tiles = 0;
+  for (int i = 0; i < count; ++i) {
+    if (i > 0 && alike) {
+      L[i] = L[0];
+    } else {
+      polyq_block b[POLYQ_MAX_BLOCKS];
+      const int nb = random_blocks(r, r.next() % 4 ? 8 : 300, b);
+      int k = 0;
+      for (int j = 0; j < nb; ++j) k += b[j].len;
+      CHECK(polyq_plan(r.next() % 4 ? r.uniform(1, 700) : r.uniform(1, 30000), k, b, nb, &L[i]) == POLYQ_OK, "plan");
+    }
+    launch_tiles += L[i].n_tiles;
+  }
+  int32_t tiles[POLYQ_MAX_BATCH], splits[POLYQ_MAX_BATCH];
+  int64_t widest = 0;
+  for (int i = 0; i < count; ++i) {
+    polyq::GemvPlan p;
+    CHECK(polyq::plan_gemv(L[i], m, launch_tiles, &p) == 0, "no plan");
+    tiles[i] = L[i].n_tiles;
+    splits[i] = p.S;
+    widest = widest > static_cast<int64_t>(tiles[i]) * p.S ? widest : static_cast<int64_t>(tiles[i]) * p.S;
+  }
+  const polyq::GemvGrid g = polyq::gemv_grid(tiles, splits, count);
+  CHECK(g.x >= 1 && g.z >= 1 && static_cast<int64_t>(g.x) * g.z <= widest, "grid %d x %d, widest linear %lld", g.x, g.z,
+        (long long)widest);
+  for (int i = 0; i < count; ++i) {
+    std::vector<int> seen(static_cast<size_t>(tiles[i]) * splits[i], 0);
+    const uint32_t magic = polyq::div_magic(static_cast<uint32_t>(tiles[i]));
+    for (int z = 0; z < g.z; ++z)
+      for (int x = 0; x < g.x; ++x) {
+        int tile = -1, s = -1;
+        polyq::gemv_place(static_cast<uint32_t>(x), static_cast<uint32_t>(z), magic, tiles[i], &tile, &s);
+        CHECK(tile >= 0 && tile < tiles[i] && s >= 0, "tile %d of %d, split %d", tile, tiles[i], s);
+        if (s < splits[i]) ++seen[static_cast<size_t>(s) * tiles[i] + tile];
+      }
+    for (size_t j = 0; j < seen.size(); ++j) CHECK(seen[j] == 1, "linear %d: place %zu reached %d times", i, j, seen[j]);
+  }
 }
 
 void check_invalid() {
@@ -229,6 +276,7 @@ int main(int argc, char** argv) {
       check_gemv_plan(L, ms[j], L.n_tiles * r.uniform(1, 40));
     }
   }
+  for (int it = 0; it < iters / 4 + 1 && !g_fail; ++it) check_gemv_grid(r);
   for (int it = 0; it < iters / 10 + 1 && !g_fail; ++it) check_alloc(r, it);
   if (g_fail) return 1;
   printf("plan_check ok: seed %llu, %d layouts\n", static_cast<unsigned long long>(seed), iters);
