@@ -65,9 +65,9 @@ struct GemvItem {
   int32_t pad;
   int32_t bits[POLYQ_MAX_BLOCKS];
   int32_t chunk_begin[POLYQ_MAX_BLOCKS];
-  int32_t chunks[POLYQ_MAX_BLOCKS];
+  int32_t chunks[POLYQ_MAX_BLOCKS];      // first wave with an extra group << 16 | chunks (at most 32768)
   int32_t wave_begin[POLYQ_MAX_BLOCKS];  // first wave (per tile) of each block; INT32_MAX past the last
-  int32_t share[POLYQ_MAX_BLOCKS];       // groups per wave: quotient << 16 | remainder (share_begin)
+  int32_t share[POLYQ_MAX_BLOCKS];       // groups per wave: q << 16 | r (share_begin)
   int32_t tile_bytes[POLYQ_MAX_BLOCKS];
   int64_t block_offset[POLYQ_MAX_BLOCKS];
 };
@@ -488,10 +488,11 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
   const int first = __builtin_popcount(static_cast<uint32_t>(reached) & ((1u << POLYQ_MAX_BLOCKS) - 1u)) - 1;
   auto block_field = [&](size_t offset) { return kfield<int32_t>(kv, static_cast<int>(offset / 4) + first); };
   const int fb = block_field(offsetof(GemvItem, bits)), fcb = block_field(offsetof(GemvItem, chunk_begin));
-  const int fnch = block_field(offsetof(GemvItem, chunks)), ftb = block_field(offsetof(GemvItem, tile_bytes));
+  const int fch = block_field(offsetof(GemvItem, chunks)), ftb = block_field(offsetof(GemvItem, tile_bytes));
   const int share = block_field(offsetof(GemvItem, share)), j0 = w - block_field(offsetof(GemvItem, wave_begin));
   const bool has_work = w < ITEM(int32_t, waves_total);
-  const int g0 = share_begin(share >> 16, share & 0xFFFF, j0), g1 = share_begin(share >> 16, share & 0xFFFF, j0 + 1);
+  const int q = share >> 16, r = share & 0xFFFF, t = fch >> 16, fnch = fch & 0xFFFF;
+  const int g0 = share_begin(q, r, t, j0), g1 = g0 + q + share_extra(r, t, j0);
   const int fl0 = has_work ? kChunksPerGroup * g0 : 0, fl1 = has_work ? min(kChunksPerGroup * g1, fnch) : 0;
   // record of a group: 256 bytes of metadata (b <= 8) + 4 chunk slices of 256 b bytes
   const int frb = (fb <= 8 ? kMetaBytes : 0) + kChunksPerGroup * 64 * 4 * fb;
@@ -1068,7 +1069,7 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
       const int nch = L.block[b].len / kChunk, ngr = (nch + kChunksPerGroup - 1) / kChunksPerGroup;
       g.bits[b] = L.block[b].bits;
       g.chunk_begin[b] = L.k_begin[b] / kChunk;
-      g.chunks[b] = nch;
+      g.chunks[b] = share_first_extra(nch, p.waves[b]) << 16 | nch;
       g.wave_begin[b] = w0;
       g.share[b] = (ngr / p.waves[b]) << 16 | (ngr % p.waves[b]);  // ngr <= 8192, waves <= 4096
       w0 += p.waves[b];

@@ -83,9 +83,24 @@ __host__ __device__ inline void gemv_place(uint32_t x, uint32_t z, uint32_t magi
   *split = turn + static_cast<int>(z);
 }
 
-// A block's groups over its waves: the first r of nw waves take q + 1 groups, the
-// others q (q = groups / nw, r = groups mod nw); the first group of wave j.
-__host__ __device__ inline int share_begin(int q, int r, int j) { return j * q + (j < r ? j : r); }
+// A block's groups over its nw waves: q = groups / nw each and one more for r =
+// groups mod nw of them, the waves t .. t + r - 1; the first group of wave j is
+// share_begin, it has q + share_extra.  The first waves take the rest (t = 0), but a
+// single group too many goes to the last wave where the block's last group is a
+// partial one: nine chunks over two waves are 4 + 5 and not 8 + 1 (512 channels, one
+// token: 4.25 us instead of 4.55; giving the rest to the last waves whatever r is
+// made 16-token launches up to 5 % slower).
+inline int share_first_extra(int chunks, int nw) {
+  const int groups = (chunks + kChunksPerGroup - 1) / kChunksPerGroup;
+  return groups % nw == 1 && chunks % kChunksPerGroup != 0 ? nw - 1 : 0;
+}
+__host__ __device__ inline int share_begin(int q, int r, int t, int j) {
+  const int past = j > t ? j - t : 0;
+  return j * q + (past < r ? past : r);
+}
+__host__ __device__ inline int share_extra(int r, int t, int j) {
+  return static_cast<unsigned>(j - t) < static_cast<unsigned>(r) ? 1 : 0;
+}
 
 // Chunk range [lo, hi) of wave w of every tile: waves are handed to the blocks
 // in order (waves[i] to block i, starting at wave w0[i]) and a block's groups
@@ -107,8 +122,9 @@ inline void wave_range(int w, int nblocks, int n_chunks, const Blk& blk, int* lo
   if (w >= w0 + nw) return;
   const int cb = blk.cb(i), nch = blk.ce(i) - cb;
   const int ngr = (nch + kChunksPerGroup - 1) / kChunksPerGroup, j = w - w0;
-  const int a = kChunksPerGroup * share_begin(ngr / nw, ngr % nw, j);
-  const int b = kChunksPerGroup * share_begin(ngr / nw, ngr % nw, j + 1);
+  const int q = ngr / nw, r = ngr % nw, t = share_first_extra(nch, nw);
+  const int a = kChunksPerGroup * share_begin(q, r, t, j);
+  const int b = a + kChunksPerGroup * (q + share_extra(r, t, j));
   *lo = cb + (a < nch ? a : nch);
   *hi = cb + (b < nch ? b : nch);
 }

@@ -96,7 +96,7 @@ void check_gemv_plan(const polyq_layout& L, int m, int launch_tiles) {
   }
   CHECK(sum <= p.S * p.W, "waves %d > %d", sum, p.S * p.W);
   const polyq::LayoutBlocks blk{&L, p.waves};
-  std::vector<int> seen(L.n_chunks, 0);
+  std::vector<int> seen(L.n_chunks, 0), widest(L.nblocks, 0);
   int worst = 0;
   for (int w = 0; w < p.S * p.W; ++w) {
     int a = 0, b = 0, bi = -2;
@@ -109,6 +109,14 @@ void check_gemv_plan(const polyq_layout& L, int m, int launch_tiles) {
     CHECK((a - cb) % 4 == 0 && (b == ce || (b - cb) % 4 == 0), "wave %d not on group boundaries", w);
     for (int c = a; c < b; ++c) ++seen[c];
     worst = b - a > worst ? b - a : worst;
+    widest[bi] = b - a > widest[bi] ? b - a : widest[bi];
+  }
+  // no wave has more of a block than an even split of its groups has to give
+  // one of them: a single group too many is the partial one, where there is one
+  for (int i = 0; i < L.nblocks; ++i) {
+    const int nch = L.block[i].len / 32, groups = (nch + 3) / 4, q = groups / p.waves[i], r = groups % p.waves[i];
+    const int most = r == 1 ? 4 * q + (nch + 3) % 4 + 1 : r > 1 ? 4 * (q + 1) : 4 * q;
+    CHECK(widest[i] <= most, "block %d of %d chunks over %d waves: %d chunks in one", i, nch, p.waves[i], widest[i]);
   }
   for (int c = 0; c < L.n_chunks; ++c) CHECK(seen[c] == 1, "chunk %d covered %d times (m=%d)", c, seen[c], m);
   CHECK(worst == p.lds_chunks, "lds_chunks %d, widest range %d", p.lds_chunks, worst);
