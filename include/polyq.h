@@ -286,11 +286,10 @@ polyq_status polyq_gemv_batch_noalloc(const polyq_gemv_item* items, int32_t coun
  *   entry are ignored.  The split sums are added in a fixed order, so results
  *   do not depend on scheduling.
  * Computed with bf16 MFMA and fp32 accumulation: (q - z) enters as one exact
- * bf16 value when z is an integer in [0, 255]; for any other fp16 z, q - z is
- * formed in fp32 from exact operands with one rounding (relative error at most
- * 2^-24) and enters as the bf16 pair hi + lo (together within 2^-16 relative of
- * q - z); the group scale is applied in fp32; a 16-bit channel enters as the
- * exact bf16 pair hi + lo of its fp16 weight.  |y - y_ref| <= 1e-3 *
+ * bf16 value when z is an integer in [0, 255]; for any other fp16 z, q - zi
+ * does, zi the nearest such integer, and s (zi - z) times the sum of the group's
+ * activations is added in fp32; the group scale is applied in fp32; a 16-bit
+ * channel enters as the exact bf16 pair hi + lo of its fp16 weight.  |y - y_ref| <= 1e-3 *
  * sum |w_hat x| for any fp16 scale and zero point.
  */
 size_t polyq_gemm_workspace_bytes(const polyq_layout* layout, int32_t m, int perm_given);

@@ -32,17 +32,22 @@
 // only), a second copy of the products for full groups or for the rare zero
 // points (spills).
 //
-// Numerics.  The dequantized operand is (q - z), an integer of magnitude
-// <= 255 that bf16 holds exactly when z is an integer in [0, 255]; each
+// Numerics.  The dequantized operand is (q - zi), zi the integer in [0, 255]
+// nearest the zero point: of magnitude <= 255, which bf16 holds exactly.  Each
 // 128-channel group accumulates into its own fp32 tile, which is then scaled
 // by the row's fp16 scale s (fp32 FMA) into the output accumulator.  A code
 // field at bit f of a half-word, OR-ed with the fp16 exponent field 25 - f,
 // reads as the fp16 value 2^(10-f) + q (exact); converted to fp32 with
-// -(2^(10-f) + z) added in the same instruction it is q - z exactly for such z,
-// and so is its upper half, the bf16 value.  A 16-bit channel, or a group whose zero point
-// is not such an integer, enters as the pair hi + lo of bf16 values (a second
-// pass over the group): for fp16 weights the pair is exact; for any other z, q
-// is recovered exactly in fp32 and q - z rounds once before the split.
+// -(2^(10-f) + zi) added in the same instruction it is q - zi exactly, and so is
+// its upper half, the bf16 value.  Where a zero point of the wave's rows is not
+// its zi, a second pass over the group with weights of 1 forms the sum of its
+// activations and adds s (zi - z) times that, in fp32 (z - zi is exact): the
+// weights are not read or unpacked again, and |q - zi| + |zi - z| <= 3 |q - z|
+// bounds what the two parts round (every zero point fractional, 5120 rows x 5120
+// channels at 4 bits: 22, 70 and 233 us for 33, 512 and 2000 tokens, against 19,
+// 52 and 157 with integers; as hi + lo pairs re-read from memory 49, 135 and
+// 585).  A 16-bit channel enters as the pair hi + lo of bf16 values (two passes),
+// exact for an fp16 weight.
 #include <hip/hip_runtime.h>
 
 #include <string.h>
@@ -273,10 +278,13 @@ __device__ __forceinline__ float f16_of(uint32_t bits) {
   return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(bits)));
 }
 
-// Zero points that the packed fp16 subtraction takes exactly.
-__device__ __forceinline__ bool z_exact(uint32_t zz) {
+// The integer in [0, 255] nearest the zero point: q - zi is exact in bf16, and
+// (zi - z) times the sum of the group's activations is added apart where z is
+// not that integer itself.
+__device__ __forceinline__ float z_int(float z) { return fminf(fmaxf(rintf(z), 0.f), 255.f); }
+__device__ __forceinline__ bool z_is_int(uint32_t zz) {
   const float z0 = f16_of(zz), z1 = f16_of(zz >> 16);
-  return z0 == truncf(z0) && z0 >= 0.f && z0 <= 255.f && z1 == truncf(z1) && z1 >= 0.f && z1 <= 255.f;
+  return z0 == z_int(z0) && z1 == z_int(z1);
 }
 
 // The two halves of an fp16 pair plus c, in fp32 (v_fma_mix_f32 by 1.0: the
@@ -292,19 +300,19 @@ __device__ __forceinline__ float hi_plus(uint32_t pair, float c) {
   return d;
 }
 
-// The group's weights as bf16 A fragments (q - z), a[rr][chunk], for integer
-// zero points in [0, 255].  H is the wave's half (3 bits: the positions of a
+// The group's weights as bf16 A fragments (q - zi), a[rr][chunk]; zi is the
+// zero point, or the integer nearest it.  H is the wave's half (3 bits: the positions of a
 // sub-tile's codes depend on it; other widths take H = 0 for both).
 template <int B, int H>
 __device__ __forceinline__ void dequant(const Raw& raw, u4v (&a)[2][4]) {
-  float nc[2][4];  // -(off + z)
+  float nc[2][4];  // -(off + zi)
 #pragma unroll
   for (int rr = 0; rr < 2; ++rr) {
-    const float z = f16_of(rr ? raw.z >> 16 : raw.z);
+    const float zi = z_int(f16_of(rr ? raw.z >> 16 : raw.z));
     float off[4];
     pair_offsets<B>(2 * H + rr, off);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) nc[rr][j] = -off[j] - z;
+    for (int j = 0; j < 4; ++j) nc[rr][j] = -off[j] - zi;
   }
   // A chunk in three stages of independent instructions (a dependent VALU
   // instruction waits about twice as long as an independent one; the fences
@@ -316,8 +324,8 @@ __device__ __forceinline__ void dequant(const Raw& raw, u4v (&a)[2][4]) {
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) unpack_sub_tile<B>(sub_words<B>(&raw.w[c * chunk_words<B>()], rr), 2 * H + rr, hp[rr]);
     __builtin_amdgcn_sched_barrier(0);
-    // (off + q) - (off + z) = q - z exactly in fp32, and in its upper half
-    // (bf16: |q - z| <= 255)
+    // (off + q) - (off + zi) = q - zi exactly in fp32, and in its upper half
+    // (bf16: |q - zi| <= 255)
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr)
 #pragma unroll
@@ -331,43 +339,6 @@ __device__ __forceinline__ void dequant(const Raw& raw, u4v (&a)[2][4]) {
       a[rr][c] = u4v{hi_half_pair(lo[rr][0], hi[rr][0]), hi_half_pair(lo[rr][1], hi[rr][1]),
                      hi_half_pair(lo[rr][2], hi[rr][2]), hi_half_pair(lo[rr][3], hi[rr][3])};
   }
-}
-
-// One chunk with any other zero points: (off + q) - off = q exactly, then
-// q - z rounds once; its hi or lo bf16 part.
-template <int B, int H>
-__device__ __forceinline__ void dequant_any(const uint32_t* w, uint32_t zz, bool lo, u4v (&out)[2]) {
-#pragma unroll
-  for (int rr = 0; rr < 2; ++rr) {
-    const float z = f16_of(rr ? zz >> 16 : zz);
-    float off[4], v[8];
-    uint32_t hp[4];
-    pair_offsets<B>(2 * H + rr, off);
-    unpack_sub_tile<B>(sub_words<B>(w, rr), 2 * H + rr, hp);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const h2 d = __builtin_bit_cast(h2, hp[j]);
-      v[2 * j] = (static_cast<float>(d.x) - off[j]) - z;
-      v[2 * j + 1] = (static_cast<float>(d.y) - off[j]) - z;
-    }
-    out[rr] = bf16_part(v, lo);
-  }
-}
-
-// The same for chunk c of a group re-read from memory.
-template <int B>
-__device__ __forceinline__ void reload_any(__amdgpu_buffer_rsrc_t rs, int lane, int h, int rec, int c, bool lo,
-                                           u4v (&out)[2]) {
-  const int voff = slice_voff<B>(lane, h), so = rec + kMetaBytes + c * 256 * B;
-  const uint32_t zz = __builtin_amdgcn_raw_buffer_load_b32(rs, (lane & 15) * 8 + 4 * h, rec, 0);
-  uint32_t w[4];
-#pragma unroll
-  for (int i = 0; i < (B == 3 ? 3 : chunk_words<B>()); ++i)
-    w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff + 4 * i, so, 0);
-  if (B == 3 && h != 0)
-    dequant_any<B, 1>(w, zz, lo, out);
-  else
-    dequant_any<B, 0>(w, zz, lo, out);
 }
 
 // Dword `dw` of a 64-dword argument record held one dword per lane, as a
@@ -499,21 +470,27 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmBatchArgs a) {
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) T[j][rr] = f4{0.f, 0.f, 0.f, 0.f};
 
-  // The hi or lo fragments of a group with a zero point that is not an integer
-  // in [0, 255], re-read from memory.
-  auto reload = [&](auto b_tag, __amdgpu_buffer_rsrc_t rs, int rec, int nch, bool lo) __attribute__((always_inline)) {
-    constexpr int B = decltype(b_tag)::value;
-#pragma unroll 1
-    for (int c = 0; c < 4; ++c) {  // rotates: after four rounds chunk c is in slot c
-      u4v o[2];
-      reload_any<B>(rs, lane, h, rec, min(c, nch - 1), lo, o);
+  // The second pass over a group with a zero point that is not an integer in
+  // [0, 255]: weights of 1, so that the products are the sums of the activations,
+  // and s (zi - z) for the scale.  (z and s re-read: the registers of the loads
+  // ahead have taken their place, and a pair held over the products would spill.)
+  auto rest_of_zero_points = [&](__amdgpu_buffer_rsrc_t rs, int rec) __attribute__((always_inline)) {
+    int l = lane;
+    asm volatile("" : "+v"(l));  // the addresses are formed here, not kept through the products
+    uint32_t z[4];
 #pragma unroll
-      for (int rr = 0; rr < 2; ++rr) {
-        af[rr][0] = af[rr][1];
-        af[rr][1] = af[rr][2];
-        af[rr][2] = af[rr][3];
-        af[rr][3] = o[rr];
+    for (int e = 0; e < 4; ++e)
+      z[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, (4 * (l >> 4) + e) * 8 + 4 * h, rec, 0);
+    const u4v s = __builtin_bit_cast(u4v, __builtin_amdgcn_raw_buffer_load_b128(rs, 128 + (l >> 4) * 32 + 16 * h, rec, 0));
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float zf = f16_of(rr ? z[e] >> 16 : z[e]);
+        sc[rr][e] = f16_of(s[2 * rr + e / 2] >> (16 * (e & 1))) * (z_int(zf) - zf);
       }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) af[rr][c] = u4v{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
     }
   };
   // All products of one group, in sets of up to four token tiles: the set's
@@ -600,7 +577,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmBatchArgs a) {
     advance(wx);
     auto step = [&](Raw& raw) __attribute__((always_inline)) {
       if (h == 0) __syncthreads();
-      const bool exact = __all(z_exact(raw.z));
+      const bool exact = __all(z_is_int(raw.z));
 #pragma unroll
       for (int rr = 0; rr < 2; ++rr)
 #pragma unroll
@@ -613,12 +590,12 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmBatchArgs a) {
       if (h != 0) __syncthreads();
 #pragma unroll 1
       for (int pass = 0;; ++pass) {
-        if (__builtin_expect(!exact, 0)) {
+        if (__builtin_expect(pass != 0, 0)) {
           const int cb = cur.block;
-          reload(b_tag,
-                 make_rsrc(packed + ITEM_AT(off, cb) + static_cast<int64_t>(tile_ok ? tile : 0) * ITEM_AT(tb, cb),
-                           tile_ok ? static_cast<uint32_t>(ITEM_AT(tb, cb)) : 0u),
-                 ((cur.chan - ITEM_AT(k0, cb)) / kGroup) * (kMetaBytes + 1024 * B), nch_of(cur), pass != 0);
+          rest_of_zero_points(
+              make_rsrc(packed + ITEM_AT(off, cb) + static_cast<int64_t>(tile_ok ? tile : 0) * ITEM_AT(tb, cb),
+                        tile_ok ? static_cast<uint32_t>(ITEM_AT(tb, cb)) : 0u),
+              ((cur.chan - ITEM_AT(k0, cb)) / kGroup) * (kMetaBytes + 1024 * B));
         }
         multiply(i & 1);
         if (exact || pass) break;

@@ -255,6 +255,63 @@ def test_gemm_small_non_integer_zero_points(case):
         assert_parity(np_(y)[:, :10], y_ref[:, :10], bound[:, :10], f"gemm small z rows {case}")
 
 
+def _fractional(lin, seed):
+    """Every zero point off the integers in [0, 255]: fractions, negatives, and a
+    few past 255."""
+    g = torch.Generator().manual_seed(seed)
+    z = torch.rand(lin.zeros.shape, generator=g) * 20 - 4
+    z[:, ::3] = torch.rand(z[:, ::3].shape, generator=g) * 0.5 - 0.25
+    z[::7, 1] = 300.5
+    lin.zeros = z.half()
+    return lin
+
+
+@pytest.mark.parametrize("m", [9, 33, 130])
+def test_gemm_fractional_zero_points_every_group(m):
+    """All groups of all bit-widths with zero points that are not integers in
+    [0, 255]: the group's two parts, (q - zi) and (zi - z), have together at most
+    three times the weight of q - z, so three times the rounding of any summation
+    order bounds the error."""
+    k = sum(ln for _, ln in STEADY)
+    lin = _fractional(random_quant_linear(130, k, STEADY, seed=5300 + m, mode="codes"), 5301)
+    x = _xb(m, k, seed=53)
+    y = packed_linear(lin).prefill(x.to(dev()))
+    torch.cuda.synchronize()
+    y_ref, bound = oracle_ref(lin, x)
+    err = np.abs(np_(y).astype(np.float64) - y_ref)
+    assert np.all(err <= 3 * (k + 2 * 20 + 32) * 2.0 ** -24 * bound)
+
+
+def test_gemm_fractional_zero_points_take_at_most_twice_as_long():
+    """A zero point that is not an integer costs a second pass over its group's
+    products, not a second unpacking: less than twice the time (of graph replays,
+    so that the host's share does not count)."""
+    n, k, m = 5120, 5120, 512
+    blocks = [(2, 1024), (3, 1536), (4, 1760), (8, 736), (16, 64)]
+    x = _xb(m, k, seed=54).to(dev())
+    times = []
+    for fractional in (False, True):
+        lin = random_quant_linear(n, k, blocks, seed=54, mode="codes")
+        pl = packed_linear(_fractional(lin, 54) if fractional else lin)
+        batch = pq.PreparedBatch("gemm", [(pl.layout, pl.packed, pl.perm, x, None)])
+        batch.run()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                batch.run()
+        runs = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            runs.append(a.elapsed_time(b))
+        times.append(sorted(runs)[4])
+    assert times[1] < 2 * times[0], times
+
+
 # Blocks of 13-16 chunks: every bit-width runs steady groups (exact-width
 # weight fetches, interleaved issue order) before its last two groups, and the
 # block ends in a partial group.
