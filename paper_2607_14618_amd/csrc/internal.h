@@ -87,12 +87,15 @@ __host__ __device__ inline void gemv_place(uint32_t x, uint32_t z, uint32_t magi
 // groups mod nw of them, the waves t .. t + r - 1; the first group of wave j is
 // share_begin, it has q + share_extra.  The first waves take the rest (t = 0), but a
 // single group too many goes to the last wave where the block's last group is a
-// partial one: nine chunks over two waves are 4 + 5 and not 8 + 1 (512 channels, one
-// token: 4.25 us instead of 4.55; giving the rest to the last waves whatever r is
-// made 16-token launches up to 5 % slower).
+// partial one and that makes the largest share smaller by more than an eighth: nine
+// chunks over two waves are 4 + 5 and not 8 + 1 (512 channels x 2048 rows, one token:
+// 4.29 us instead of 4.61).  A smaller saving does not pay (gate/up of 25600 rows at
+// 6 bits, one token: 38.9 us instead of 38.3), and the rest for the last waves
+// whatever r is made 16-token launches up to 5 % slower.
 inline int share_first_extra(int chunks, int nw) {
   const int groups = (chunks + kChunksPerGroup - 1) / kChunksPerGroup;
-  return groups % nw == 1 && chunks % kChunksPerGroup != 0 ? nw - 1 : 0;
+  const int missing = groups * kChunksPerGroup - chunks;  // of the last group
+  return groups % nw == 1 && 2 * missing > groups / nw + 1 ? nw - 1 : 0;
 }
 __host__ __device__ inline int share_begin(int q, int r, int t, int j) {
   const int past = j > t ? j - t : 0;

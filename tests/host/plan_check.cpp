@@ -112,10 +112,12 @@ void check_gemv_plan(const polyq_layout& L, int m, int launch_tiles) {
     widest[bi] = b - a > widest[bi] ? b - a : widest[bi];
   }
   // no wave has more of a block than an even split of its groups has to give
-  // one of them: a single group too many is the partial one, where there is one
+  // one of them; a single group too many is the partial one, where that saves more
+  // than an eighth of the share
   for (int i = 0; i < L.nblocks; ++i) {
     const int nch = L.block[i].len / 32, groups = (nch + 3) / 4, q = groups / p.waves[i], r = groups % p.waves[i];
-    const int most = r == 1 ? 4 * q + (nch + 3) % 4 + 1 : r > 1 ? 4 * (q + 1) : 4 * q;
+    const int partial = 4 * q + (nch + 3) % 4 + 1;
+    const int most = r == 1 && 8 * (4 * (q + 1) - partial) > 4 * (q + 1) ? partial : r > 0 ? 4 * (q + 1) : 4 * q;
     CHECK(widest[i] <= most, "block %d of %d chunks over %d waves: %d chunks in one", i, nch, p.waves[i], widest[i]);
   }
   for (int c = 0; c < L.n_chunks; ++c) CHECK(seen[c] == 1, "chunk %d covered %d times (m=%d)", c, seen[c], m);
