@@ -62,7 +62,7 @@ struct GemvItem {
   int32_t n_tiles;
   int32_t zero_offset;    // LDS offset of the work-group's zero row
   uint32_t tiles_magic;   // div_magic(n_tiles)
-  int32_t pad;
+  int32_t x_end;          // gemv_grid
   int32_t bits[POLYQ_MAX_BLOCKS];
   int32_t chunk_begin[POLYQ_MAX_BLOCKS];
   int32_t chunks[POLYQ_MAX_BLOCKS];      // first wave with an extra group << 16 | chunks (at most 32768)
@@ -72,9 +72,11 @@ struct GemvItem {
   int64_t block_offset[POLYQ_MAX_BLOCKS];
 };
 
-// The launch: work-group (x, y, z) runs a tile and split of linear y (gemv_place).
+// The launch (gemv_grid).
 struct GemvBatchArgs {
   GemvItem item[kMaxItems];
+  int32_t first_tile[kMaxItems];
+  int32_t joint;
 };
 
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
@@ -469,14 +471,24 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_kernel(const GemvBatchArgs a
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // The work-group's linear (blockIdx.y) is read with one vector load (a dword
   // per lane) and broadcast with v_readlane; scalar loads of it would miss the
-  // scalar cache line by line.
+  // scalar cache line by line.  A joint launch looks for the linear only past the
+  // first one's tiles (looked for by every work-group it took 0.1 us of each launch,
+  // and a second kernel for it 5 to 10 % of a layer's launches that alternate).
   const uint32_t* kargs = (const uint32_t*)(__builtin_amdgcn_kernarg_segment_ptr());
   static_assert(sizeof(GemvItem) == 256 && offsetof(GemvBatchArgs, item) == 0, "argument layout");
-  const uint32_t kv = kargs[blockIdx.y * 64 + lane];
+  uint32_t kv = kargs[blockIdx.y * 64 + lane];
+  int x = blockIdx.x;
+  if (x >= ITEM(int32_t, x_end)) {
+    if (a.joint == 0) return;
+    constexpr int kFirstTile = offsetof(GemvBatchArgs, first_tile) / 4;
+    const int32_t begin = static_cast<int32_t>(kargs[kFirstTile + (lane & (kMaxItems - 1))]);
+    const int linear = __builtin_popcount(static_cast<uint32_t>(__ballot(begin <= x)) & ((1u << kMaxItems) - 1u)) - 1;
+    kv = kargs[linear * 64 + lane];
+    x -= __builtin_amdgcn_readlane(begin, linear);
+  }
   const int n_tiles = ITEM(int32_t, n_tiles), S = ITEM(int32_t, S);
   int tile, s;
-  gemv_place(blockIdx.x, blockIdx.z, ITEM(uint32_t, tiles_magic), n_tiles, &tile, &s);
-  if (s >= S) return;  // this linear has fewer work-groups than the launch's widest
+  gemv_place(x, blockIdx.z, ITEM(uint32_t, tiles_magic), n_tiles, &tile, &s);
   const int m = ITEM(int32_t, m);
   // This wave's chunks [fl0, fl1) of block `first`: the block whose first wave
   // is the last one not past w (a compare of all lanes with the record's
@@ -1091,7 +1103,10 @@ extern "C" polyq_status polyq_gemv_batch(const polyq_gemv_item* items, int32_t c
                                  reinterpret_cast<uint16_t*>(ws + bp.xp_off[i]), items[i].layout->k, 0};
   launch_shuffle(jobs, njobs, m, false, hs);
   const GemvGrid grid = gemv_grid(tiles, splits, count);
-  hipLaunchKernelGGL(gemv_kernel, dim3(grid.x, count, grid.z), dim3(kWaves * 64), bp.lds, hs, a);
+  for (int i = 0; i < count; ++i) a.item[i].x_end = grid.x_end[i];
+  a.joint = grid.joint ? 1 : 0;
+  memcpy(a.first_tile, grid.first_tile, sizeof(a.first_tile));
+  hipLaunchKernelGGL(gemv_kernel, dim3(grid.x, grid.y, grid.z), dim3(kWaves * 64), bp.lds, hs, a);
   return hipGetLastError() == hipSuccess ? POLYQ_OK : POLYQ_ERR_DEVICE;
 }
 

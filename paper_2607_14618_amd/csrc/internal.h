@@ -47,36 +47,59 @@ __host__ __device__ inline uint32_t div_by_magic(uint32_t a, uint32_t magic, uin
   return hi >> div_log2(d);
 }
 
-// Grid of a decode launch: work-group (x, y, z) runs linear y, tile x mod n_tiles
-// and split x / n_tiles + z of it (gemv_place); splits at or past the linear's
-// own have nothing to do.  Flat (z = 0, x over tiles x splits of the widest
-// linear): a linear's splits are adjacent, and at most `count` times the widest
-// linear's work-groups are launched whatever the others look like.  Split by
-// split (x over the tiles, z over the splits), for linears of equal tiles and
-// splits, where it launches not one more: a CU's work-groups (256 apart) are then
-// of different splits, that is of different bit-widths, which balances a launch
-// that is resident all at once, and one of two rounds or more.  In between, a
-// second round is a mere tail, and the flat order, whose first linear is done with
-// its fix-ups by then, is the faster.  Split by split / flat, one token, 3 bits:
-// q/k/v of 5120 (720 work-groups) 13.0 / 14.3 us, of 8192 (768) 24.9 / 29.7;
-// gate/up of 13824 (864) 20.1 / 19.5, of 14336 (896) 18.1 / 17.0; 6 bits, of 25600
-// (1600) 38.0 / 39.5 (4 tokens 47.9 / 45.3, 16 tokens 74.3 / 76.2).  Unequal
-// linears in one box of the widest of each: 4096 + 2 x 1024 rows 11.1 / 9.3,
-// 131072 rows x 512 with 64 x 65536 (16 tokens) 124 / 49.
+// Grid of a decode launch: work-group (x, y, z), in one of three forms.
+//   flat: linear y, x over its tiles x splits, tiles fastest (z = 0).  At most
+//     `count` times the widest linear's work-groups, whatever the others look like.
+//   split by split, where all linears have the same number of splits: linear y, tile
+//     x, split z.
+//   joint: the same with x over the tiles of all linears (first_tile) and y = 0.
+// x_end: past it a work-group has nothing to do (flat, split by split), or belongs
+// to a later linear than the first (joint).
+// A CU's work-groups are about 256 apart in launch order and should be of different
+// splits, that is of different bit-widths, so that all CUs take equally long.  Split
+// by split they are, and in the flat order they are where one linear has about as
+// many tiles as there are CUs; the flat one is the faster where a second round is
+// begun and not half full.  Split by split / flat, one token: q/k/v of 5120 (720
+// work-groups) 13.0 / 14.3 us, of 8192 (768) 24.9 / 29.7, gate/up of 12160 (760) 18.4
+// / 19.0, of 13824 (864) 20.1 / 19.4, of 15360 (960) 21.4 / 19.5, of 25600 (1600)
+// 38.0 / 39.5 (4 tokens 47.9 / 45.3, 16 tokens 74.3 / 76.2).
+// Tiles that a narrow linear lacks cost about 2 ns each split by split; a joint
+// launch has none, but its later linears wait for two more loads, 0.2 us.  Split by
+// split / joint: 6 + 1 + 1 tiles 7.69 / 7.86 us, 48 + 12 + 12 (432 too many) 7.51 /
+// 7.37, 64 + 16 + 16 (768) 11.1 / 8.6.  Linears without a common number of splits: in
+// one box of the widest of each / flat, 131072 rows x 512 with 64 x 65536 (16
+// tokens) 124 / 49.
+constexpr int kCUs = 256;
 struct GemvGrid {
-  int32_t x, z;
+  int32_t x, y, z;
+  bool joint;
+  int32_t x_end[POLYQ_MAX_BATCH];
+  int32_t first_tile[POLYQ_MAX_BATCH];  // INT32_MAX past the last linear
 };
 inline GemvGrid gemv_grid(const int32_t* n_tiles, const int32_t* splits, int count) {
-  bool equal = true;
-  int widest = 0;
-  for (int i = 0; i < count; ++i) {
-    equal = equal && n_tiles[i] == n_tiles[0] && splits[i] == splits[0];
+  GemvGrid g;
+  bool same_splits = true;
+  int widest = 0, most = 0, tiles = 0;  // work-groups and tiles of the widest linear, tiles of all
+  for (int i = 0; i < POLYQ_MAX_BATCH; ++i) {
+    g.x_end[i] = 0;
+    g.first_tile[i] = i < count ? tiles : INT32_MAX;
+    if (i >= count) continue;
+    same_splits = same_splits && splits[i] == splits[0];
     widest = widest > n_tiles[i] * splits[i] ? widest : n_tiles[i] * splits[i];
+    most = most > n_tiles[i] ? most : n_tiles[i];
+    tiles += n_tiles[i];
   }
-  const int64_t total = static_cast<int64_t>(widest) * count;
-  if (equal && (total <= kResidentWGs || total >= 2 * kResidentWGs)) return GemvGrid{n_tiles[0], splits[0]};
-  return GemvGrid{widest, 1};
+  const int64_t total = static_cast<int64_t>(tiles) * splits[0];
+  const bool alternates = 3 * most > 2 * kCUs && 2 * most < 3 * kCUs;
+  const bool by_split = same_splits && !(alternates && total > kResidentWGs && 2 * total < 3 * kResidentWGs);
+  g.joint = by_split && static_cast<int64_t>(most) * count * splits[0] - total > kCUs;
+  for (int i = 0; i < count; ++i) g.x_end[i] = by_split ? n_tiles[i] : n_tiles[i] * splits[i];
+  g.x = g.joint ? tiles : by_split ? most : widest;
+  g.y = g.joint ? 1 : count;
+  g.z = by_split ? splits[0] : 1;
+  return g;
 }
+// Tile and split of a linear's work-group (x counted from its first tile).
 __host__ __device__ inline void gemv_place(uint32_t x, uint32_t z, uint32_t magic, int n_tiles, int* tile, int* split) {
   const int turn = static_cast<int>(div_by_magic(x, magic, static_cast<uint32_t>(n_tiles)));
   *tile = static_cast<int>(x) - turn * n_tiles;

@@ -132,12 +132,12 @@ void check_gemv_plan(const polyq_layout& L, int m, int launch_tiles) {
 // linear's (items of different n and k may not multiply each other's extremes).
 void check_gemv_grid(Rng& r) {
   const int count = r.uniform(1, POLYQ_MAX_BATCH), m = r.uniform(1, 16);
-  const bool alike = r.next() % 2 != 0;
+  const int alike = r.uniform(0, 2);  // 1: equal linears, 2: of one input (n differs)
   std::vector<polyq_layout> L(count);
   int launch_tiles = 0;
   for (int i = 0; i < count; ++i) {
     if (i > 0 && alike) {
-      L[i] = L[0];
+      CHECK(polyq_plan(alike == 1 ? L[0].n : r.uniform(1, 9000), L[0].k, L[0].block, L[0].nblocks, &L[i]) == POLYQ_OK, "plan");
     } else {
       polyq_block b[POLYQ_MAX_BLOCKS];
       const int nb = random_blocks(r, r.next() % 4 ? 8 : 300, b);
@@ -148,29 +148,74 @@ void check_gemv_grid(Rng& r) {
     launch_tiles += L[i].n_tiles;
   }
   int32_t tiles[POLYQ_MAX_BATCH], splits[POLYQ_MAX_BATCH];
-  int64_t widest = 0;
+  int64_t widest = 0, all = 0;
   for (int i = 0; i < count; ++i) {
     polyq::GemvPlan p;
     CHECK(polyq::plan_gemv(L[i], m, launch_tiles, &p) == 0, "no plan");
     tiles[i] = L[i].n_tiles;
     splits[i] = p.S;
     widest = widest > static_cast<int64_t>(tiles[i]) * p.S ? widest : static_cast<int64_t>(tiles[i]) * p.S;
+    all += static_cast<int64_t>(tiles[i]) * p.S;
   }
   const polyq::GemvGrid g = polyq::gemv_grid(tiles, splits, count);
-  CHECK(g.x >= 1 && g.z >= 1 && static_cast<int64_t>(g.x) * g.z <= widest, "grid %d x %d, widest linear %lld", g.x, g.z,
-        (long long)widest);
+  const int64_t launched = static_cast<int64_t>(g.x) * g.y * g.z;
+  CHECK(g.x >= 1 && g.y == (g.joint ? 1 : count) && launched >= all && launched <= (g.joint ? all : g.z > 1 ? all + polyq::kCUs : widest * count),
+        "grid %d x %d x %d for %lld work-groups, widest linear %lld", g.x, g.y, g.z, (long long)all, (long long)widest);
   for (int i = 0; i < count; ++i) {
     std::vector<int> seen(static_cast<size_t>(tiles[i]) * splits[i], 0);
     const uint32_t magic = polyq::div_magic(static_cast<uint32_t>(tiles[i]));
     for (int z = 0; z < g.z; ++z)
-      for (int x = 0; x < g.x; ++x) {
-        int tile = -1, s = -1;
+      for (int x0 = 0; x0 < g.x; ++x0) {
+        int tile = -1, s = -1, x = x0;
+        if (g.joint) {  // the last linear that begins at or before x
+          int linear = 0;
+          for (int j = 1; j < POLYQ_MAX_BATCH; ++j) linear += g.first_tile[j] <= x ? 1 : 0;
+          if (linear != i) continue;
+          CHECK((i > 0) == (x >= g.x_end[0]), "x %d, linear %d, x_end %d", x, i, g.x_end[0]);
+          x -= g.first_tile[i];
+        } else if (x >= g.x_end[i]) {
+          continue;
+        }
         polyq::gemv_place(static_cast<uint32_t>(x), static_cast<uint32_t>(z), magic, tiles[i], &tile, &s);
-        CHECK(tile >= 0 && tile < tiles[i] && s >= 0, "tile %d of %d, split %d", tile, tiles[i], s);
-        if (s < splits[i]) ++seen[static_cast<size_t>(s) * tiles[i] + tile];
+        CHECK(tile >= 0 && tile < tiles[i] && s >= 0 && s < splits[i], "tile %d of %d, split %d", tile, tiles[i], s);
+        ++seen[static_cast<size_t>(s) * tiles[i] + tile];
       }
     for (size_t j = 0; j < seen.size(); ++j) CHECK(seen[j] == 1, "linear %d: place %zu reached %d times", i, j, seen[j]);
   }
+}
+
+// The grid form of the launches that tests/test_gpu_gemv.py runs (its GRIDS): rows of
+// each linear, k, the form.
+void check_grid_forms() {
+  enum Form { kFlat, kBySplit, kJoint };
+  struct {
+    int count, n[3], k[3];
+    Form form;
+  } const cases[] = {
+      {3, {4096, 1024, 1000}, {2048, 2048, 2048}, kJoint}, {3, {1000, 4096, 65}, {2048, 2048, 2048}, kJoint},
+      {3, {2048, 2048, 2048}, {2048, 2048, 2048}, kBySplit}, {3, {400, 64, 30}, {2048, 2048, 2048}, kBySplit},
+      {2, {13824, 13800, 0}, {1024, 1024, 0}, kFlat}, {3, {4096, 64, 130}, {1024, 20480, 2048}, kFlat},
+  };
+  for (const auto& c : cases)
+    for (int m = 1; m <= 5; m += 4) {
+      int32_t tiles[3], splits[3], launch_tiles = 0;
+      polyq_layout L[3];
+      for (int i = 0; i < c.count; ++i) {
+        const int unit = (c.k[i] - 32) / 32, b2 = unit * 45 / 100 | 1, b3 = unit * 35 / 100 | 1, b4 = unit * 15 / 100 | 1;
+        const polyq_block b[5] = {{2, 32 * b2}, {3, 32 * b3}, {4, 32 * b4}, {8, 32 * (unit - b2 - b3 - b4)}, {16, 32}};
+        CHECK(polyq_plan(c.n[i], c.k[i], b, 5, &L[i]) == POLYQ_OK, "plan n=%d k=%d", c.n[i], c.k[i]);
+        launch_tiles += L[i].n_tiles;
+      }
+      for (int i = 0; i < c.count; ++i) {
+        polyq::GemvPlan p;
+        CHECK(polyq::plan_gemv(L[i], m, launch_tiles, &p) == 0, "no plan");
+        tiles[i] = L[i].n_tiles;
+        splits[i] = p.S;
+      }
+      const polyq::GemvGrid g = polyq::gemv_grid(tiles, splits, c.count);
+      const Form form = g.joint ? kJoint : g.z > 1 ? kBySplit : kFlat;
+      CHECK(form == c.form, "n=%d, %d linears, m=%d: form %d, not %d", c.n[0], c.count, m, form, c.form);
+    }
 }
 
 void check_invalid() {
@@ -264,6 +309,7 @@ int main(int argc, char** argv) {
   const int iters = argc > 2 ? atoi(argv[2]) : 300;
   Rng r{seed};
   check_invalid();
+  if (!g_fail) check_grid_forms();
   for (int it = 0; it < iters && !g_fail; ++it) {
     polyq_block b[POLYQ_MAX_BLOCKS];
     // mostly short layers, some long ones up to the largest k

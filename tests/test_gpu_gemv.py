@@ -431,3 +431,48 @@ def test_gemv_more_than_65536_row_tiles():
     rows = np.unique(np.concatenate([np.arange(n - 256, n), rng.integers(0, n, 512)]))
     y_ref, bound = oracle_ref(lin, x, rows=rows)
     assert_parity(np_(y)[:, rows], y_ref, bound, "n_tiles=65537")
+
+
+def _mix(k):
+    """2, 3, 4 and 8 bit blocks and 32 channels at 16 bits, each ending in a partial group."""
+    unit = (k - 32) // 32
+    b2, b3, b4 = unit * 45 // 100 | 1, unit * 35 // 100 | 1, unit * 15 // 100 | 1
+    return [(2, 32 * b2), (3, 32 * b3), (4, 32 * b4), (8, 32 * (unit - b2 - b3 - b4)), (16, 32)]
+
+
+# Row counts (and k) of one launch's linears, by the form of its grid: see GRIDS in
+# tests/host/plan_check.cpp, which asserts the form of each.
+GRIDS = {
+    "joint": [(4096, 2048), (1024, 2048), (1000, 2048)],
+    "joint, narrow first": [(1000, 2048), (4096, 2048), (65, 2048)],
+    "split by split": [(2048, 2048)] * 3,
+    "split by split, unequal": [(400, 2048), (64, 2048), (30, 2048)],
+    "flat, second round begun": [(13824, 1024), (13800, 1024)],
+    "flat, unequal splits": [(4096, 1024), (64, 20480), (130, 2048)],
+}
+
+
+@pytest.mark.parametrize("form", list(GRIDS))
+@pytest.mark.parametrize("m", [1, 5])
+def test_gemv_batch_every_grid_form(form, m):
+    """Every linear of a launch gets every one of its tiles and splits, whatever
+    form the launch's grid takes; twice, so that each split's fix-up left its
+    counters as it found them."""
+    lins, pls, xs = [], [], []
+    for i, (n, k) in enumerate(GRIDS[form]):
+        lin = random_quant_linear(n, k, _mix(k), seed=900 + i, mode="codes")
+        lins.append(lin)
+        pls.append(packed_linear(lin))
+        xs.append(_x(m, k, seed=90 + i))
+    batch = pq.PreparedBatch("gemv", [(pl.layout, pl.packed, pl.perm, x.to(dev()), None) for pl, x in zip(pls, xs)])
+    first = [y.clone() for y in batch.run()]
+    for y in batch.ys:
+        y.fill_(float("nan"))
+    batch.run()
+    torch.cuda.synchronize()
+    for lin, x, y, y0 in zip(lins, xs, batch.ys, first):
+        assert torch.equal(y, y0)
+        assert bool(torch.isfinite(y).all())
+        rows = np.unique(np.concatenate([np.arange(0, lin.n, 61), np.arange(max(0, lin.n - 70), lin.n)]))
+        y_ref, bound = oracle_ref(lin, x, rows=rows)
+        assert_parity(np_(y)[:, rows], y_ref, bound, f"{form} n={lin.n} m={m}")
