@@ -68,11 +68,10 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u3v __attribute__((ext_vector_type(3)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 
-constexpr int kThreads = 512;      // 8 waves
-constexpr int kTilesWG = 4;        // packed tiles per work-group (two waves each)
-constexpr int kTok = 16;           // tokens of one MFMA
-constexpr int kMaxNT = 8;          // token tiles per work-group (kernel instances 1 .. kMaxNT)
-constexpr int kMaxSplits = 32;
+constexpr int kThreads = 512;         // 8 waves
+constexpr int kTilesWG = kGemmTiles;  // packed tiles per work-group (two waves each)
+constexpr int kTok = kGemmTokens;     // tokens of one MFMA
+constexpr int kMaxNT = kGemmMaxNT;    // token tiles per work-group (kernel instances 1 .. kMaxNT)
 
 // One linear of a launch: 64 dwords, so that one vector load (a dword per lane)
 // fetches it and v_readlane reads its fields at run-time indexes: scalar loads
@@ -741,58 +740,12 @@ size_t permuted_bytes(const polyq_layout& L, int32_t m) {
   return static_cast<size_t>(align_up(static_cast<int64_t>(m) * L.k * 2, 256));
 }
 
-int groups_of(const polyq_layout& L) {
-  int g = 0;
-  for (int i = 0; i < L.nblocks; ++i) g += (L.block[i].len + kGroup - 1) / kGroup;
-  return g;
-}
-
 struct GemmPlan {
   int64_t region[POLYQ_MAX_BATCH];   // workspace offset of item i's copy x', or -1
   size_t partial[POLYQ_MAX_BATCH];   // workspace offset of its partial sums (splits > 1)
   size_t total;
-  int nt, splits;
-  int32_t m_tiles;
+  GemmShape shape;
 };
-
-// K splits of a launch of `wg` work-groups per split: as many as keep it within
-// one round of one work-group per CU, with at least four groups each.  More
-// splits add partial sums and the fixed cost of a work-group faster than they
-// add parallel work: 33 tokens through a 13B-class layer take 165, 119, 153 and
-// 145 us when planned for 128, 256, 384 and 512 work-groups (512 tokens: 622,
-// 457, 528, 511), and 143, 148, 146 and 138 us with at least 1, 2, 3 and 4
-// groups.
-int64_t splits_for(int64_t wg, int groups, int most) {
-  return std::max<int64_t>(1, std::min<int64_t>({256 / wg, most, groups / 4}));
-}
-
-// Token tiles of a work-group (nt, 16 tokens each) and K splits: the least
-// estimated time, rounds of 256 work-groups x (11 + nt) / splits.  A group takes
-// a work-group about (11 + nt) units (1.9 us at 3 tiles, 2.6 us at 8): mostly the
-// chain that does not depend on the tokens, so the largest nt wins unless a
-// smaller one fills a round that would leave CUs idle: 512 tokens x 10240 rows x
-// 5120 channels take 86 us at nt = 6 (240 work-groups) and 97 at 8 (160), 77
-// tokens x 1357 rows x 2976 channels 20.6 at 1 and 28.0 at 5.  Ties: the larger.
-void plan_shape(const polyq_gemv_item* items, int32_t count, int32_t m, int most_splits, int* nt, int32_t* m_tiles,
-                int* splits) {
-  const int64_t tiles = (static_cast<int64_t>(m) + kTok - 1) / kTok;
-  int64_t rows = 0;
-  int groups = 0;
-  for (int i = 0; i < count; ++i) {
-    rows += (items[i].layout->n_tiles + kTilesWG - 1) / kTilesWG;
-    groups = std::max(groups, groups_of(*items[i].layout));
-  }
-  double best = 0;
-  for (int t = static_cast<int>(std::min<int64_t>(kMaxNT, tiles)); t >= 1; --t) {
-    const int64_t mt = (tiles + t - 1) / t, s = splits_for(rows * mt, groups, most_splits);
-    const double cost = static_cast<double>((rows * mt * s + 255) / 256) * (11 + t) / static_cast<double>(s);
-    if (best != 0 && cost >= best) continue;
-    best = cost;
-    *nt = t;
-    *m_tiles = static_cast<int32_t>(mt);
-    *splits = static_cast<int>(s);
-  }
-}
 
 // Workspace of a batch: one clustered copy x' = x[:, perm] (times the channel
 // factors of Eq. 8) per distinct (x, perm, factors) of the items with a
@@ -823,16 +776,18 @@ polyq_status plan_gemm_batch(const polyq_gemv_item* items, int32_t count, int32_
   auto partial_bytes = [&](int i, int splits) {
     return static_cast<size_t>(align_up(static_cast<int64_t>(splits) * m * items[i].layout->n * 4, 256));
   };
-  int most = kMaxSplits;
+  int most = kGemmMaxSplits;
   for (; count > 1 && most > 1; --most) {
     size_t need = off;
     for (int i = 0; i < count; ++i) need += partial_bytes(i, most);
     if (need <= room) break;
   }
-  plan_shape(items, count, m, most, &p->nt, &p->m_tiles, &p->splits);
+  const polyq_layout* layouts[POLYQ_MAX_BATCH];
+  for (int i = 0; i < count; ++i) layouts[i] = items[i].layout;
+  p->shape = gemm_shape(layouts, count, m, most);
   for (int i = 0; i < count; ++i) {
     p->partial[i] = off;
-    if (p->splits > 1) off += partial_bytes(i, p->splits);
+    if (p->shape.splits > 1) off += partial_bytes(i, p->shape.splits);
   }
   p->total = off;
   return POLYQ_OK;
@@ -876,8 +831,8 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
   memset(&a, 0, sizeof(a));
   a.count = count;
   a.m = m;
-  a.splits = p.splits;
-  a.m_tiles = p.m_tiles;
+  a.splits = p.shape.splits;
+  a.m_tiles = p.shape.m_tiles;
   for (int i = 0; i < count; ++i) {
     const polyq_gemv_item& itm = items[i];
     const polyq_layout& L = *itm.layout;
@@ -893,7 +848,7 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
   for (int i = 0; i < count; ++i) {
     a.wg_begin[i] = static_cast<int32_t>(wg);
     a.item[i].row_blocks = (items[i].layout->n_tiles + kTilesWG - 1) / kTilesWG;
-    wg += static_cast<int64_t>(a.item[i].row_blocks) * p.m_tiles * p.splits;
+    wg += static_cast<int64_t>(a.item[i].row_blocks) * p.shape.m_tiles * p.shape.splits;
     if (wg > 0x7FFFFFFF) return POLYQ_ERR_CAPACITY;
   }
   for (int i = count; i <= POLYQ_MAX_BATCH; ++i) a.wg_begin[i] = static_cast<int32_t>(wg);
@@ -912,7 +867,7 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
   launch_shuffle(jobs, njobs, m, true, st);
   SumArgs sum;
   memset(&sum, 0, sizeof(sum));
-  sum.splits = p.splits;
+  sum.splits = p.shape.splits;
   int64_t widest = 0;
   for (int i = 0; i < count; ++i) {
     const polyq_gemv_item& itm = items[i];
@@ -924,12 +879,12 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
     widest = std::max(widest, sum.count[i]);
     g.packed = static_cast<const uint8_t*>(itm.packed);
     g.x = p.region[i] >= 0 ? reinterpret_cast<const uint16_t*>(ws + p.region[i]) : itm.x;
-    g.y = p.splits > 1 ? reinterpret_cast<float*>(ws + p.partial[i]) : itm.y;
+    g.y = p.shape.splits > 1 ? reinterpret_cast<float*>(ws + p.partial[i]) : itm.y;
     g.n = L.n;
     g.k = L.k;
     g.nblocks = L.nblocks;
     g.n_tiles = L.n_tiles;
-    g.groups = groups_of(L);
+    g.groups = layout_groups(L);
     g.y_vec = (L.n % 4 == 0 && reinterpret_cast<uintptr_t>(g.y) % 16 == 0) ? 1 : 0;
     for (int b = 0; b < L.nblocks; ++b) {
       g.bits[b] = L.block[b].bits;
@@ -939,8 +894,8 @@ extern "C" polyq_status polyq_gemm_batch(const polyq_gemm_item* items, int32_t c
       g.tb[b] = static_cast<int32_t>(L.tile_bytes[b]);
     }
   }
-  launch_gemm<1>(p.nt, wg, a, st);
-  if (p.splits > 1)
+  launch_gemm<1>(p.shape.nt, wg, a, st);
+  if (p.shape.splits > 1)
     hipLaunchKernelGGL(sum_splits_kernel, dim3(static_cast<unsigned>((widest + 1023) / 1024), count), dim3(256), 0, st,
                        sum);
   return hipGetLastError() == hipSuccess ? POLYQ_OK : POLYQ_ERR_DEVICE;

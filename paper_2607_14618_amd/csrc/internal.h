@@ -164,6 +164,22 @@ int plan_gemv(const polyq_layout& L, int32_t m, int32_t launch_tiles, GemvPlan* 
 // per tile (padded to 256 B) followed by the partials [S][m][n_tiles*64] fp32.
 size_t gemv_workspace_for(const polyq_layout& L, int32_t m, const GemvPlan& p);
 
+// Prefill launch: a work-group multiplies kGemmTiles packed tiles by `nt` token
+// tiles (kGemmTokens each), `m_tiles` work-groups cover the tokens and K is split
+// into `splits` ranges of whole groups (at most `most`).
+constexpr int kGemmTiles = 4;
+constexpr int kGemmTokens = 16;
+constexpr int kGemmMaxNT = 8;
+constexpr int kGemmMaxSplits = 32;
+struct GemmShape {
+  int nt, splits;
+  int32_t m_tiles;
+};
+GemmShape gemm_shape(const polyq_layout* const* layouts, int count, int32_t m, int most);
+
+// Groups of a layout, of every bit-width (16 included).
+int layout_groups(const polyq_layout& L);
+
 // True when `L` is exactly what polyq_plan produces for its own n, k, blocks.
 bool layout_is_valid(const polyq_layout* L);
 

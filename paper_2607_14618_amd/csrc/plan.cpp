@@ -200,6 +200,48 @@ int plan_gemv(const polyq_layout& L, int32_t m, int32_t launch_tiles, GemvPlan* 
   }
 }
 
+int layout_groups(const polyq_layout& L) {
+  int g = 0;
+  for (int i = 0; i < L.nblocks; ++i) g += (L.block[i].len + kGroup - 1) / kGroup;
+  return g;
+}
+
+// The least estimated time in us.  A round of one work-group per CU takes 1 + 0.12 nt
+// for each group of its K range (mostly the chain that does not depend on the tokens)
+// and 1.5 + 0.75 nt around them; splits cost the sum launch (1.1 and 0.25 for each
+// split) and their partial sums' way to memory and back (0.21 per MB each).  Least
+// squares over 780 random launches (64 to 84000 rows in all, 256 to 22400 channels, 1
+// to 2100 tokens, each with every token tile and up to a dozen splits): the plan taken
+// is 1.7 % off the best of those on average, 21 % at most.  Without the splits' cost and
+// with at least four groups each it was 10 and 47 % off, which lost against the
+// unsplit 256-token tiles before: 111 tokens x 3149 rows x 6880 channels 39.9 -> 45.3
+// us (7 tiles, 13 splits).
+GemmShape gemm_shape(const polyq_layout* const* layouts, int count, int32_t m, int most) {
+  const int64_t tiles = (static_cast<int64_t>(m) + kGemmTokens - 1) / kGemmTokens;
+  int64_t rows = 0, outputs = 0;
+  int groups = 0;
+  for (int i = 0; i < count; ++i) {
+    rows += (layouts[i]->n_tiles + kGemmTiles - 1) / kGemmTiles;
+    outputs += layouts[i]->n;
+    groups = std::max(groups, layout_groups(*layouts[i]));
+  }
+  const double sum_mb = 2 * 4e-6 * static_cast<double>(outputs) * m;
+  GemmShape best{};
+  double least = 0;
+  for (int t = static_cast<int>(std::min<int64_t>(kGemmMaxNT, tiles)); t >= 1; --t) {
+    const int64_t mt = (tiles + t - 1) / t, wg = rows * mt;
+    const int64_t split_end = std::min<int64_t>({most, groups / 2, kCUs / wg});  // one round at most
+    for (int s = 1; s == 1 || s <= split_end; ++s) {
+      const double round = (groups + s - 1) / s * (1 + 0.12 * t) + 1.5 + 0.75 * t;
+      const double cost = static_cast<double>((wg * s + kCUs - 1) / kCUs) * round + (s > 1 ? 1.1 + s * (0.25 + 0.21 * sum_mb) : 0);
+      if (least != 0 && cost >= least) continue;
+      least = cost;
+      best = GemmShape{t, s, static_cast<int32_t>(mt)};
+    }
+  }
+  return best;
+}
+
 size_t gemv_workspace_for(const polyq_layout& L, int32_t m, const GemvPlan& p) {
   if (p.S <= 1) return 0;
   const size_t counters = static_cast<size_t>(align_up(static_cast<int64_t>(L.n_tiles) * 4, 256));

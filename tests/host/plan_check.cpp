@@ -3,7 +3,7 @@
 // invalid ones, the decode-GEMV work split (every chunk of a layer covered by
 // exactly one wave, each wave inside one block and starting on one of its
 // group boundaries, LDS within the work-group budget), the decode grid of a
-// batch, and the allocation's
+// batch, the prefill launch's token tiles and splits, and the allocation's
 // outputs (palette bit-widths, the budget never exceeded by waterfilling,
 // counts on the quantum after matching, a permutation from clustering).
 // Built with g++ and the address and undefined-behaviour sanitizers by
@@ -14,6 +14,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "internal.h"
@@ -218,6 +219,70 @@ void check_grid_forms() {
     }
 }
 
+// Prefill launches: token tiles of a work-group and K splits.
+struct GemmForm {
+  int n, m, blocks;  // blocks: index into kGemmBlocks
+  int nt;
+  bool split;
+};
+const polyq_block kGemmBlocks[][5] = {{{2, 1440}, {3, 1472}, {4, 1504}, {8, 1536}, {16, 416}},
+                                      {{2, 416}, {3, 448}, {4, 480}, {8, 512}, {16, 416}},
+                                      {{2, 1376}, {3, 2048}, {4, 2400}, {8, 992}, {16, 64}},
+                                      {{2, 160}, {3, 256}, {4, 288}, {8, 96}, {16, 32}}};
+polyq::GemmShape gemm_shape_of(int n, int m, int blocks) {
+  const polyq_block* b = kGemmBlocks[blocks];
+  polyq_layout L;
+  const polyq_layout* l = &L;
+  if (polyq_plan(n, b[0].len + b[1].len + b[2].len + b[3].len + b[4].len, b, 5, &L) != POLYQ_OK) return {};
+  return polyq::gemm_shape(&l, 1, m, polyq::kGemmMaxSplits);
+}
+// The forms that tests/test_gpu_gemm.py runs (its GEMM_FORMS).
+void check_gemm_forms() {
+  const GemmForm forms[] = {
+      {2051, 11, 0, 1, true},  {1157, 183, 0, 2, true}, {1157, 337, 0, 3, true}, {2051, 374, 0, 4, true},
+      {2051, 449, 0, 5, true}, {3205, 361, 0, 6, true}, {3205, 321, 0, 7, true}, {3205, 481, 0, 8, true},
+      {40963, 3, 1, 1, false}, {3205, 577, 1, 2, false}, {5381, 401, 1, 3, false}, {5381, 529, 1, 4, false},
+      {8195, 449, 1, 5, false}, {8195, 561, 1, 6, false}, {12805, 481, 1, 7, false}, {12805, 561, 1, 8, false}};
+  for (const auto& f : forms) {
+    const polyq::GemmShape s = gemm_shape_of(f.n, f.m, f.blocks);
+    CHECK(s.nt == f.nt && (s.splits > 1) == f.split, "n=%d m=%d: %d token tiles, %d splits", f.n, f.m, s.nt, s.splits);
+  }
+  // Splits pay for the sum launch and their partial sums' way to memory and back: not
+  // 13 of them for 111 tokens x 3149 rows x 6880 channels (45.3 us; 39.9 with the
+  // kernel of one 256-token tile; 4 token tiles and 8 splits: less than either), and
+  // none for 164 tokens x 14307 rows x 832 channels (35.0 us in two, 25.4 in one).
+  polyq::GemmShape s = gemm_shape_of(3149, 111, 2);
+  CHECK(s.splits > 1 && s.splits <= 8, "%d token tiles, %d splits", s.nt, s.splits);
+  s = gemm_shape_of(14307, 164, 3);
+  CHECK(s.splits == 1, "%d token tiles, %d splits", s.nt, s.splits);
+}
+// Any launch: its tokens covered by work-groups that all have some, no more splits than
+// given or than half the groups, more than one only within one round.
+void check_gemm_shape(Rng& r) {
+  const int count = r.uniform(1, POLYQ_MAX_BATCH), m = r.next() % 2 ? r.uniform(1, 300) : r.uniform(1, 100000);
+  const int most = r.uniform(1, polyq::kGemmMaxSplits);
+  std::vector<polyq_layout> L(count);
+  const polyq_layout* l[POLYQ_MAX_BATCH];
+  int64_t rows = 0;
+  int groups = 0;
+  for (int i = 0; i < count; ++i) {
+    polyq_block b[POLYQ_MAX_BLOCKS];
+    const int nb = random_blocks(r, r.next() % 4 ? 8 : 300, b);
+    int k = 0;
+    for (int j = 0; j < nb; ++j) k += b[j].len;
+    CHECK(polyq_plan(r.next() % 4 ? r.uniform(1, 700) : r.uniform(1, POLYQ_MAX_N), k, b, nb, &L[i]) == POLYQ_OK, "plan");
+    l[i] = &L[i];
+    rows += (L[i].n_tiles + 3) / 4;
+    groups = std::max(groups, polyq::layout_groups(L[i]));
+  }
+  const polyq::GemmShape s = polyq::gemm_shape(l, count, m, most);
+  const int64_t tiles = (static_cast<int64_t>(m) + 15) / 16;
+  CHECK(s.nt >= 1 && s.nt <= polyq::kGemmMaxNT && s.nt * static_cast<int64_t>(s.m_tiles) >= tiles &&
+            s.nt * (s.m_tiles - 1ll) < tiles, "m=%d: %d x %d token tiles", m, s.m_tiles, s.nt);
+  CHECK(s.splits >= 1 && s.splits <= most && (s.splits == 1 || (2 * s.splits <= groups && rows * s.m_tiles * s.splits <= polyq::kCUs)),
+        "%d splits of %d groups, %lld row blocks, %d token tiles", s.splits, groups, (long long)rows, s.m_tiles);
+}
+
 void check_invalid() {
   polyq_layout L;
   polyq_block ok[2] = {{2, 64}, {16, 64}};
@@ -310,6 +375,7 @@ int main(int argc, char** argv) {
   Rng r{seed};
   check_invalid();
   if (!g_fail) check_grid_forms();
+  if (!g_fail) check_gemm_forms();
   for (int it = 0; it < iters && !g_fail; ++it) {
     polyq_block b[POLYQ_MAX_BLOCKS];
     // mostly short layers, some long ones up to the largest k
@@ -333,6 +399,7 @@ int main(int argc, char** argv) {
     }
   }
   for (int it = 0; it < iters / 4 + 1 && !g_fail; ++it) check_gemv_grid(r);
+  for (int it = 0; it < iters && !g_fail; ++it) check_gemm_shape(r);
   for (int it = 0; it < iters / 10 + 1 && !g_fail; ++it) check_alloc(r, it);
   if (g_fail) return 1;
   printf("plan_check ok: seed %llu, %d layouts\n", static_cast<unsigned long long>(seed), iters);
