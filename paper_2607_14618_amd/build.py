@@ -28,10 +28,13 @@ CFLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", f"-I{INCLUDE}"
 # work-group per CU the compiler would otherwise move one there), and its
 # loop invariants in the loops that use them (hoisted to the kernel entry they
 # would stay live across every bit-width's store and overflow the 256
-# registers a wave of an 8-wave work-group can have).
+# registers a wave of an 8-wave work-group can have).  Its branch targets start on
+# 32 bytes: 16384 rows x 4096 channels of 8 bits at 512 tokens 76.6 -> 76.1 us, of the
+# 4-bit mix 78.5 -> 78.0 (on 64 bytes 76.5 and 78.7, on 128 77.4 and 79.3).
 EXTRA = {"gemv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
          "gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-disable-promote-alloca-to-lds",
-                      "-mllvm", "-disable-machine-licm"]}
+                      "-mllvm", "-disable-machine-licm",
+                      "-mllvm", "-align-all-nofallthru-blocks=5"]}
 
 
 def _compile(src: str) -> str:

@@ -281,10 +281,6 @@ __device__ __forceinline__ float f16_of(uint32_t bits) {
 // (zi - z) times the sum of the group's activations is added apart where z is
 // not that integer itself.
 __device__ __forceinline__ float z_int(float z) { return fminf(fmaxf(rintf(z), 0.f), 255.f); }
-__device__ __forceinline__ bool z_is_int(uint32_t zz) {
-  const float z0 = f16_of(zz), z1 = f16_of(zz >> 16);
-  return z0 == z_int(z0) && z1 == z_int(z1);
-}
 
 // The two halves of an fp16 pair plus c, in fp32 (v_fma_mix_f32 by 1.0: the
 // conversion and the addition in one instruction each).
@@ -299,19 +295,18 @@ __device__ __forceinline__ float hi_plus(uint32_t pair, float c) {
   return d;
 }
 
-// The group's weights as bf16 A fragments (q - zi), a[rr][chunk]; zi is the
-// zero point, or the integer nearest it.  H is the wave's half (3 bits: the positions of a
-// sub-tile's codes depend on it; other widths take H = 0 for both).
+// The group's weights as bf16 A fragments (q - zi), a[rr][chunk].  H is the wave's
+// half (3 bits: the positions of a sub-tile's codes depend on it; other widths take
+// H = 0 for both).
 template <int B, int H>
-__device__ __forceinline__ void dequant(const Raw& raw, u4v (&a)[2][4]) {
+__device__ __forceinline__ void dequant(const Raw& raw, const float (&zi)[2], u4v (&a)[2][4]) {
   float nc[2][4];  // -(off + zi)
 #pragma unroll
   for (int rr = 0; rr < 2; ++rr) {
-    const float zi = z_int(f16_of(rr ? raw.z >> 16 : raw.z));
     float off[4];
     pair_offsets<B>(2 * H + rr, off);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) nc[rr][j] = -off[j] - zi;
+    for (int j = 0; j < 4; ++j) nc[rr][j] = -off[j] - zi[rr];
   }
   // A chunk in three stages of independent instructions (a dependent VALU
   // instruction waits about twice as long as an independent one; the fences
@@ -576,13 +571,16 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmBatchArgs a) {
     advance(wx);
     auto step = [&](Raw& raw) __attribute__((always_inline)) {
       if (h == 0) __syncthreads();
-      const bool exact = __all(z_is_int(raw.z));
+      const float z0 = f16_of(raw.z), z1 = f16_of(raw.z >> 16);
+      float zi[2] = {z_int(z0), z_int(z1)};
+      asm("" : "+v"(zi[0]), "+v"(zi[1]));  // formed once (the compiler would round in fp16 too)
+      const bool exact = __all(z0 == zi[0] && z1 == zi[1]);
 #pragma unroll
       for (int rr = 0; rr < 2; ++rr)
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[rr][e] = f16_of(raw.s[2 * rr + e / 2] >> (16 * (e & 1)));
-      if (B == 3 && h != 0) dequant<B, 1>(raw, af);
-      else dequant<B, 0>(raw, af);
+      if (B == 3 && h != 0) dequant<B, 1>(raw, zi, af);
+      else dequant<B, 0>(raw, zi, af);
       load_x(wx.chan, nch_of(wx));
       issue_raw<B>(raw, wrs, lane, h, rec, nch_of(wr));
       advance_weights();
