@@ -71,7 +71,10 @@ __device__ __forceinline__ void pack_slice(const uint4 (&u)[4], uint32_t* __rest
 // bytes of a row that a chunk takes and the 64 that the next one takes come from
 // the same 128-byte line at about the same time: with one launch per block and
 // quantity and tiles fastest that layer took 73.6 us; it takes 41.8 (4.3 TB/s).
+// A 16-bit chunk's stores go through LDS (all of it 16 bits: 13824 x 5120 72.5 -> 53.7
+// us, 5.3 TB/s; 2031 x 22208 43.1 -> 30.1).
 __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs a) {
+  __shared__ uint4 copies[kChunksPerGroup][256];  // 16 bits: a chunk of each wave
   const int g = static_cast<int>(blockIdx.x % static_cast<unsigned>(a.groups));
   const int t = a.tile0 + static_cast<int>(blockIdx.x / static_cast<unsigned>(a.groups));
   int b = 0;
@@ -105,7 +108,18 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs a) {
     case 3: pack_slice<3>(u, dst); break;
     case 4: pack_slice<4>(u, dst); break;
     case 8: pack_slice<8>(u, dst); break;
-    default: pack_slice<16>(u, dst); break;
+    default: {
+      // a slice is its rows' 16 bytes as they are: swapped between the lanes, so that
+      // a store writes 1 KB in a row and not 16 bytes of every 64
+#pragma unroll
+      for (int r = 0; r < 4; ++r) copies[c][lane * 4 + (r ^ ((lane >> 1) & 3))] = u[r];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      uint4* chunk = reinterpret_cast<uint4*>(record + c * kTileRows * kChunk * 2);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) chunk[i * 64 + lane] = copies[c][(i * 64 + lane) ^ ((lane >> 3) & 3)];
+    }
   }
 }
 
