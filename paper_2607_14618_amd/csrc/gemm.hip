@@ -18,17 +18,16 @@
 // 747 us instead of 681, gate/up of 2000 tokens x 13824 rows x 5120 channels).
 //
 // What bounds it: the issue slots and dependent chains of the two waves a SIMD
-// holds (248 registers at NT = 8).  A 16x16x32 MFMA takes two of its sixteen
-// clocks' four issue slots, so a group's 64 products and about 270 vector
-// instructions per wave (dequantization 150, folds 64) need 3200 of the 4900
-// clocks that it takes; the matrix pipes are 40 % busy.  Loads are not it: with
-// every load hitting the cache the launch is 3 % faster.  Measured against the
-// kernel before (256 tokens x 128 rows, both operands staged in LDS, whatever
-// M is), packed size and mix as stated: 33 tokens through a 13B-class layer (4
-// launches, 4 bits) 306 -> 131 us, 512 tokens 538 -> 451 us (720 TFLOP/s), 2000
-// tokens of gate/up at 3 bits 749 -> 649 us (870 TFLOP/s).  Also tried: four
-// waves per work-group and two work-groups per CU (734 us instead of 681), one
-// loop for all bit-widths (735: the weights' loads then go one group ahead
+// holds (254 registers at NT = 8).  A group is 64 products and, per wave, 123 to 173
+// vector instructions of dequantization (8 to 3 bits) and 64 of folds, one behind
+// the other in a wave; a product takes two of its sixteen clocks' four issue slots.
+// Loads are not it: with every load hitting the cache the launch is 3 % faster.
+// Measured against the kernel before (256 tokens x 128 rows, both operands staged in
+// LDS, whatever M is), packed size and mix as stated: 33 tokens through a 13B-class
+// layer (4 launches, 4 bits) 306 -> 127 us, 512 tokens 543 -> 452 us (719 TFLOP/s),
+// 2000 tokens of gate/up at 3 bits 771 -> 668 us (847 TFLOP/s).  Also tried: four
+// waves per work-group and two work-groups per CU (734 us instead of 681 for the last),
+// one loop for all bit-widths (735: the weights' loads then go one group ahead
 // only), a second copy of the products for full groups or for the rare zero
 // points (spills).
 //
@@ -609,7 +608,10 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmBatchArgs a) {
   };
   // The groups of the 16-bit block: fp16 weights, hi then lo parts.  (Both
   // parts come from registers: re-reading the weights for each, with the
-  // conversion in integer instructions, cost about 10 us per work-group.)
+  // conversion in integer instructions, cost about 10 us per work-group.  The next
+  // group's weights loaded behind the second part's products: 6394 rows x 18304
+  // channels of 16 bits, 2047 tokens, 1200 us instead of 1146, since the loop of the two
+  // parts then waits for every load; with the parts unrolled it spills from NT = 6 on.)
   auto run_block16 = [&]() __attribute__((always_inline)) {
     sc[0] = sc[1] = f4{1.f, 1.f, 1.f, 1.f};
     for (;;) {
