@@ -70,7 +70,7 @@ __device__ __forceinline__ void pack_slice(const uint4 (&u)[4], uint32_t* __rest
 // a 13824 x 5120 layer).  Groups vary fastest over the grid, so that the 64
 // bytes of a row that a chunk takes and the 64 that the next one takes come from
 // the same 128-byte line at about the same time: with one launch per block and
-// quantity and tiles fastest that layer took 73.6 us; it takes 41.8 (4.3 TB/s).
+// quantity and tiles fastest that layer took 73.6 us; it takes 39.7 (4.6 TB/s).
 // A 16-bit chunk's stores go through LDS (all of it 16 bits: 13824 x 5120 72.5 -> 53.7
 // us, 5.3 TB/s; 2031 x 22208 43.1 -> 30.1).
 __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs a) {
